@@ -23,6 +23,7 @@ struct Csr {
 //   load  : stored value -> accumulator (boolean NULL array = all true)
 //   mul   : semiring multiply,  add : semiring add
 //   lds_add: atomic semiring add into LDS (workgroup scope)
+//   store_stream: store that does not displace other data from the caches
 // ---------------------------------------------------------------------------
 enum { SR_F64 = 0, SR_I64 = 1, SR_BOOL = 2 };
 
@@ -46,6 +47,9 @@ template <> struct Sr<SR_F64> {
         __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __device__ static inline void store(void* out, int64_t p, acc_t v) { ((double*)out)[p] = v; }
+    __device__ static inline void store_stream(void* out, int64_t p, acc_t v) {
+        __builtin_nontemporal_store(v, (double*)out + p);
+    }
 };
 
 template <> struct Sr<SR_I64> {
@@ -62,6 +66,9 @@ template <> struct Sr<SR_I64> {
     __device__ static inline void store(void* out, int64_t p, acc_t v) {
         ((int64_t*)out)[p] = (int64_t)v;
     }
+    __device__ static inline void store_stream(void* out, int64_t p, acc_t v) {
+        __builtin_nontemporal_store((int64_t)v, (int64_t*)out + p);
+    }
 };
 
 template <> struct Sr<SR_BOOL> {
@@ -77,6 +84,9 @@ template <> struct Sr<SR_BOOL> {
     }
     __device__ static inline void store(void* out, int64_t p, acc_t v) {
         ((uint8_t*)out)[p] = (uint8_t)v;
+    }
+    __device__ static inline void store_stream(void* out, int64_t p, acc_t v) {
+        __builtin_nontemporal_store((uint8_t)v, (uint8_t*)out + p);
     }
 };
 
@@ -227,10 +237,13 @@ __device__ inline int lanes_below(uint64_t mask) {
 // Workgroup exclusive scan of one value per thread.  `tmp` must hold
 // NT/64 + 1 elements of T.  Returns the exclusive prefix; *total gets the
 // sum over the workgroup.  Contains barriers: all threads must call it.
+// Every wave scans the wave totals itself (one LDS read per lane), so there
+// is no serial walk over them by one thread.
 // ---------------------------------------------------------------------------
 template <int NT, typename T>
 __device__ inline T block_exclusive_scan(T v, T* total, T* tmp) {
     constexpr int NW = NT / SPG_WAVE;
+    static_assert(NW <= SPG_WAVE, "one lane per wave total");
     const int lane = lane_id();
     const int wid = threadIdx.x / SPG_WAVE;
     T inc = wave_inclusive_scan_add(v);
@@ -240,20 +253,34 @@ __device__ inline T block_exclusive_scan(T v, T* total, T* tmp) {
     }
     if (lane == SPG_WAVE - 1) tmp[wid] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        T run = 0;
-        for (int w = 0; w < NW; ++w) {
-            T t = tmp[w];
-            tmp[w] = run;
-            run += t;
-        }
-        tmp[NW] = run;
-    }
+    const T w = lane < NW ? tmp[lane] : T(0);
+    const T winc = wave_inclusive_scan_add(w);
+    *total = __shfl(winc, NW - 1, SPG_WAVE);
+    const T before = __shfl(winc - w, wid, SPG_WAVE);
     __syncthreads();
-    T res = inc - v + tmp[wid];
-    *total = tmp[NW];
-    __syncthreads();
-    return res;
+    return before + inc - v;
+}
+
+// Makes the values known to be used here: a load (or the arithmetic on it)
+// whose only use is inside a later branch is otherwise sunk into that branch
+// by the compiler, which then waits for the memory there, one product at a
+// time, instead of with all the loads in flight.
+__device__ inline void pin(int32_t& v) { asm volatile("" : "+v"(v)); }
+__device__ inline void pin(uint32_t& v) { asm volatile("" : "+v"(v)); }
+__device__ inline void pin(int64_t& v) { asm volatile("" : "+v"(v)); }
+__device__ inline void pin(unsigned long long& v) { asm volatile("" : "+v"(v)); }
+__device__ inline void pin(double& v) { asm volatile("" : "+v"(v)); }
+
+// A column (or an output rank) and a value.
+template <typename V>
+struct BEntry {
+    int32_t col;
+    V val;
+};
+template <typename V>
+__device__ inline void pin(BEntry<V>& e) {
+    pin(e.col);
+    pin(e.val);
 }
 
 // Workgroup min and max of one value per thread (tmp: 2*(NT/64) elements).

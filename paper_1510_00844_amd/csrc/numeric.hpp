@@ -24,12 +24,6 @@
 
 namespace spg {
 
-template <typename V>
-struct BEntry {
-    int32_t col;
-    V val;
-};
-
 // Where a row's output goes: its count is rp[i+1] - rp[i]; it starts at
 // pos[i] when pos is given (rows of a gathered sub-product written straight
 // into the full product), else at rp[i].
@@ -464,17 +458,18 @@ __global__ void __launch_bounds__(NT) k_num_dense(Csr A, Csr B, const int32_t* r
     int64_t off = c_rp.off(i);
     const int64_t row_end = off + c_rp.count(i);
     const int c_first = 0, c_last = P;
-    // Rows with at most NT entries in the window keep their A entry (column
+    // Rows with at most one batch of entries in the window keep their A entry (column
     // k, start of B(k,:), position reached in B(k,:)) in registers across
     // the chunks, so each chunk costs one split-table load per entry.
-    const bool single = end - beg <= NT;
+    const bool single = end - beg <= ProductLds<NT>::EB;
     int64_t my_k = 0, my_rs = 0;
     int32_t my_cur = 0;
+    V my_av = S::zero();
     if (single && beg + (int64_t)threadIdx.x < end) {
         const int64_t p = beg + threadIdx.x;
         my_k = A.col[p];
         my_rs = B.rp[my_k];
-        s_av[threadIdx.x] = S::load(A.val, p);
+        my_av = S::load(A.val, p);
     }
     __syncthreads();
     for (int c = c_first; c < c_last; ++c) {
@@ -500,9 +495,7 @@ __global__ void __launch_bounds__(NT) k_num_dense(Csr A, Csr B, const int32_t* r
                     }
                 }
             },
-            [&](int t, int64_t p) {
-                if (!single) s_av[t] = S::load(A.val, p);
-            },
+            [&](int t, int64_t p) { s_av[t] = single ? my_av : S::load(A.val, p); },
             [&](int64_t q) { return BEntry<V>{B.col[q], S::load(B.val, q)}; },
             [&](int t, const BEntry<V>& x) {
                 const int32_t j = x.col - cbase;
@@ -535,90 +528,159 @@ __global__ void __launch_bounds__(NT) k_num_dense(Csr A, Csr B, const int32_t* r
     }
 }
 
-// Copy nw bitmap words from global memory into the low halves of the LDS
-// words bw[] with coalesced loads, the first 8 per thread issued together.
-template <int NT>
-__device__ inline void stage_bitmap_words(const uint32_t* src, int nw, uint64_t* bw) {
-    constexpr int K = 8;
-    uint32_t v[K];
+__device__ inline int32_t uniform32(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline int64_t uniform64(int64_t v) {
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v));
+}
+// A bitmap's words spread over a workgroup, at most KW per thread: wave w
+// holds the 64 keff words from 64 keff w, word k of a lane 64 k further, so
+// the loads are coalesced and a wave's words are consecutive.
+template <int NT, int KW>
+__device__ inline void fetch_words(const uint32_t* src, int nw, uint32_t* wv) {
+    const int keff = nw < NT * KW ? (nw + NT - 1) / NT : KW;
+    const int w0 = (int)(threadIdx.x / SPG_WAVE) * SPG_WAVE * keff + lane_id();
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int w = threadIdx.x + k * NT;
-        v[k] = w < nw ? src[w] : 0u;
+    for (int k = 0; k < KW; ++k) {
+        const int w = w0 + k * SPG_WAVE;
+        wv[k] = k < keff && w < nw ? __builtin_nontemporal_load(src + w) : 0u;
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int w = threadIdx.x + k * NT;
-        if (w < nw) bw[w] = v[k];
-    }
-    for (int w = threadIdx.x + K * NT; w < nw; w += NT) bw[w] = src[w];
 }
 
-// Packs the staged bitmap words (low half: the bits; high half: the number
-// of set bits in all earlier words) and writes the column cbase + 32 w + b of
-// every set bit, in order, to out[0, cnt).  Each thread scans a contiguous
-// run of words and drops its columns into `acc` (LDS, used as int32 staging:
-// it holds at least cnt accumulators of 4 or 8 bytes); the block then copies
-// them out with consecutive threads on consecutive positions, so the global
-// stores are coalesced, and leaves acc[0, cnt) zero.  Contains barriers.
-template <int NT, typename V>
-__device__ inline void pack_words_write_cols(uint64_t* bw, int nw, int32_t cbase, int32_t cnt, V* acc,
-                                             int32_t* out, int32_t* red) {
-    int32_t* stage = reinterpret_cast<int32_t*>(acc);
-    const int wpt = (nw + NT - 1) / NT;
-    const int w0 = threadIdx.x * wpt;
-    const int w1 = w0 + wpt < nw ? w0 + wpt : nw;
-    int32_t part = 0;
-    for (int w = w0; w < w1; ++w) part += __popc((uint32_t)bw[w]);
-    int32_t dummy;
-    int32_t run = block_exclusive_scan<NT, int32_t>(part, &dummy, red);
-    for (int w = w0; w < w1; ++w) {
-        uint32_t bits = (uint32_t)bw[w];
-        bw[w] = ((uint64_t)(uint32_t)run << 32) | bits;
-        while (bits) {
-            const int b = __ffs(bits) - 1;
-            bits &= bits - 1;
-            if (run < cnt) stage[run] = cbase + w * 32 + b;
-            ++run;
+// Ranks of a bitmap of nw words (at most 65535 set bits): bits[w] = word w,
+// pfx[w] = set bits of all earlier words, and stage[r] = the column cbase +
+// 32 w + b of the r-th set bit.  wv holds the words' first NT KW (from
+// fetch_words); more are fetched here.  The counts are scanned in registers
+// (a wave's words are consecutive), so one exchange of the wave totals through
+// tot (NT / 64 words of LDS) is all that the waves wait for.  Contains
+// barriers; the results are visible after the next one.
+template <int NT, int KW>
+__device__ inline void rank_words(const uint32_t* src, int nw, uint32_t* wv, uint32_t* bits, uint16_t* pfx,
+                                  int32_t* stage, int32_t cbase, int32_t* tot) {
+    constexpr int NW = NT / SPG_WAVE;
+    const int lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / SPG_WAVE));
+    int32_t before = 0;
+    for (int t0 = 0; t0 < nw; t0 += NT * KW) {
+        const int tw = nw - t0;
+        const int keff = tw < NT * KW ? (tw + NT - 1) / NT : KW;
+        if (t0 > 0) {
+            fetch_words<NT, KW>(src + t0, tw, wv);
+            __syncthreads();  // the last tile's totals are read
+        }
+        int32_t pre[KW], run = 0;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) {
+            if (k >= keff) break;
+            const int32_t pc = __popc(wv[k]);
+            const int32_t inc = wave_inclusive_scan_add(pc);
+            pre[k] = run + inc - pc;
+            run += __builtin_amdgcn_readlane(inc, SPG_WAVE - 1);
+        }
+        if (lane == 0) tot[wid] = run;
+        __syncthreads();
+        const int32_t wt = lane < NW ? tot[lane] : 0;
+        const int32_t ws = wave_inclusive_scan_add(wt);
+        const int32_t wbase = before + __builtin_amdgcn_readlane(ws - wt, wid);
+        before += __builtin_amdgcn_readlane(ws, NW - 1);
+        const int w0 = t0 + wid * SPG_WAVE * keff + lane;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) {
+            const int w = w0 + k * SPG_WAVE;
+            if (k >= keff) break;
+            if (w >= nw) break;
+            uint32_t b = wv[k];
+            int32_t r = wbase + pre[k];
+            bits[w] = b;
+            pfx[w] = (uint16_t)r;
+            const int32_t c = cbase + w * 32;
+            while (b) {
+                stage[r++] = c + __builtin_ctz(b);
+                b &= b - 1;
+            }
         }
     }
-    __syncthreads();
-    // accumulator e holds staged positions [K e, K e + K): one thread reads
-    // them, stores them and clears the accumulator
-    constexpr int K = (int)(sizeof(V) / sizeof(int32_t));
-    const int ne = (cnt + K - 1) / K;
-    for (int e = threadIdx.x; e < ne; e += NT) {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (K * e + k < cnt) out[K * e + k] = stage[K * e + k];
-        acc[e] = V(0);
-    }
-    for (int e = ne + threadIdx.x; e < cnt; e += NT) acc[e] = V(0);
 }
 
-// Dynamic LDS: nwords 64-bit words (bits in the low half, count of set bits
-// in all earlier words in the high half), then `cap` accumulators.
+// The staged columns to out[0, cnt), consecutive threads on consecutive
+// positions, leaving the accumulators acc[0, cnt), whose bytes held them, zero.
+template <int NT, typename V>
+__device__ inline void write_staged_cols(V* acc, int32_t cnt, int32_t* out) {
+    const int32_t* stage = reinterpret_cast<const int32_t*>(acc);
+    // accumulator e holds staged positions [K e, K e + K): one thread reads
+    // them, stores them (one store when all K are outputs) and clears the
+    // accumulator; four of them are read before any is stored
+    constexpr int K = (int)(sizeof(V) / sizeof(int32_t));
+    static_assert(K == 1 || K == 2, "4- or 8-byte accumulators");
+    constexpr int U = 4;
+    for (int e0 = threadIdx.x; K * e0 < cnt; e0 += U * NT) {
+        int32_t c[U][K];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int r = K * (e0 + u * NT) + k;
+                c[u][k] = stage[r < cnt ? r : 0];
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = K * (e0 + u * NT);
+            if (r + K <= cnt) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) __builtin_nontemporal_store(c[u][k], out + r + k);
+            } else if (r < cnt) {
+                __builtin_nontemporal_store(c[u][0], out + r);
+            }
+        }
+    }
+    __syncthreads();  // every staged column is read
+    for (int e = threadIdx.x; e < cnt; e += NT) acc[e] = V(0);
+}
+
+// The accumulators acc[0, cnt) to out[off, off + cnt), four read before any
+// is stored.
+template <int SR, int NT>
+__device__ inline void write_values(const typename Sr<SR>::acc_t* acc, int32_t cnt, void* out, int64_t off) {
+    typedef typename Sr<SR>::acc_t V;
+    constexpr int U = 4;
+    for (int r0 = threadIdx.x; r0 < cnt; r0 += U * NT) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = acc[r0 + u * NT < cnt ? r0 + u * NT : 0];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (r0 + u * NT < cnt) Sr<SR>::store_stream(out, off + r0 + u * NT, v[u]);
+    }
+}
+
+// Dynamic LDS: `cap` accumulators, then nwords bitmap words and their 16-bit
+// prefixes (6 bytes per 32 columns: with 8, the packed words kept a third
+// workgroup per CU out at 65536 columns and 4096 outputs).
 template <int SR, int NT, int GM>
 __global__ void __launch_bounds__(NT) k_num_rank(Csr A, Csr B, const int32_t* rows,
                                                  const int64_t* a_beg, const int64_t* a_end,
                                                  const uint32_t* bm_save, const int32_t* heavy_idx,
-                                                 int32_t nwords, OutRows c_rp, int32_t* c_col,
+                                                 int32_t nwords, int32_t cap, OutRows c_rp, int32_t* c_col,
                                                  void* c_val) {
     typedef Sr<SR> S;
     typedef typename S::acc_t V;
+    constexpr int KW = 4;  // bitmap words per thread held in registers
     extern __shared__ uint64_t dyn[];
-    uint64_t* bw = dyn;
-    V* acc = reinterpret_cast<V*>(dyn + nwords);
-    __shared__ V s_av[NT];
+    V* acc = reinterpret_cast<V*>(dyn);
+    uint32_t* bits = reinterpret_cast<uint32_t*>(acc + cap);
+    uint16_t* pfx = reinterpret_cast<uint16_t*>(bits + nwords);
+    __shared__ V s_av[ProductLds<NT>::EB];
     __shared__ ProductLds<NT> L;
-    __shared__ int32_t red[NT / SPG_WAVE + 1];
+    __shared__ int32_t tot[NT / SPG_WAVE];
     const int64_t i = rows[blockIdx.x];
     const int64_t off = c_rp.off(i);
     const int32_t cnt = (int32_t)c_rp.count(i);
     const uint32_t* src = bm_save + (int64_t)heavy_idx[i] * nwords;
-    stage_bitmap_words<NT>(src, nwords, bw);
+    uint32_t wv[KW];
+    fetch_words<NT, KW>(src, nwords, wv);
+    rank_words<NT, KW>(src, nwords, wv, bits, pfx, reinterpret_cast<int32_t*>(acc), 0, tot);
     __syncthreads();
-    pack_words_write_cols<NT>(bw, nwords, 0, cnt, acc, c_col + off, red);
+    write_staged_cols<NT>(acc, cnt, c_col + off);
     __syncthreads();
     for_each_product_gm<NT, GM>(
         a_beg[i], a_end[i], L,
@@ -631,12 +693,13 @@ __global__ void __launch_bounds__(NT) k_num_rank(Csr A, Csr B, const int32_t* ro
         [&](int64_t q) { return BEntry<V>{B.col[q], S::load(B.val, q)}; },
         [&](int t, const BEntry<V>& x) {
             const uint32_t j = (uint32_t)x.col;
-            const uint64_t wd = bw[j >> 5];
-            const int32_t rank = (int32_t)(wd >> 32) + __popc((uint32_t)wd & ((1u << (j & 31)) - 1u));
-            if (rank < cnt) S::lds_add(&acc[rank], S::mul(s_av[t], x.val));
+            const int32_t rank = (int32_t)pfx[j >> 5] + __popc(bits[j >> 5] & ((1u << (j & 31)) - 1u));
+            return BEntry<V>{rank, S::mul(s_av[t], x.val)};
+        },
+        [&](const BEntry<V>& y) {
+            if (y.col < cnt) S::lds_add(&acc[y.col], y.val);
         });
-    if (c_val)
-        for (int r = threadIdx.x; r < cnt; r += NT) S::store(c_val, off + r, acc[r]);
+    if (c_val) write_values<SR, NT>(acc, cnt, c_val, off);
 }
 
 // Rank chunks: the rows of the bitmap pass that are too large for the
@@ -645,43 +708,81 @@ __global__ void __launch_bounds__(NT) k_num_rank(Csr A, Csr B, const int32_t* ro
 // and at most G chunks; an item accumulates in LDS at index = rank inside
 // the item, with its B segments taken from the split table.
 struct RankItem {
-    int32_t r;      // index into the bin's row list
+    int32_t row;    // the row
+    int32_t slot;   // its saved bitmap
     int32_t c0, c1; // chunk range [c0, c1)
     int32_t cnt;    // outputs of the item
+    int32_t annz;   // the row's A entries
+    int64_t a_beg;  // the first of them
     int64_t roff;   // outputs of the row before the item
 };
 
-// Chunks per rank-chunk item: about RC outputs at the bin's mean density
-// (cnnz outputs over nr rows of `chunks` chunks), at most chunk_group and
-// `chunks`, and no more than the LDS holds (G*W/32 packed words + RC
-// values + static_lds <= max_lds).  Integer arithmetic, so the host (sizing
+__device__ inline RankItem uniform_item(const RankItem& x) {
+    return RankItem{uniform32(x.row), uniform32(x.slot), uniform32(x.c0), uniform32(x.c1), uniform32(x.cnt),
+                    uniform32(x.annz), uniform64(x.a_beg), uniform64(x.roff)};
+}
+
+// Size of the rank-chunk items: at most RC outputs over at most G chunks of W
+// columns, so that an item holds about RC outputs at the bin's mean density
+// (cnnz outputs over nr rows of `chunks` chunks).  An item's fixed work (its
+// bitmap, its A entries' B segments, its barriers) and the partly used cache
+// lines at both ends of each B segment weigh less the larger it is, so RC
+// grows from 4096 (at least W: a chunk may be full) as long as the same
+// number of workgroups fits a CU's LDS.  R-MAT scale 19 (G = 26): RC 4096
+// 53.4 ms, 5120 49.6, 5376 with one workgroup per CU 71.5 (whole product);
+// scale 16: 4096 and 4608 the same.  Integer arithmetic, so the host (sizing
 // the launch) and the device (forming the items) agree.
-__host__ __device__ inline int32_t rankc_group(int64_t nr, int64_t cnnz, int32_t chunks, int32_t RC, int32_t chunk_group,
-                                               int32_t W, int64_t static_lds, int64_t max_lds) {
-    int64_t G = cnnz > 0 ? (2 * (int64_t)RC * nr * chunks + cnnz) / (2 * cnnz) : chunks;
-    if (G > chunks) G = chunks;
-    if (G > chunk_group) G = chunk_group;
-    if (G < 1) G = 1;
-    while (G > 1 && G * (W / 32) * 8 + (int64_t)RC * 8 + static_lds > max_lds) --G;
-    return (int32_t)G;
+constexpr int RANKC_NT = 512;
+constexpr int64_t RANKC_STATIC_LDS = (int64_t)(8 * ProductLds<RANKC_NT>::EB + sizeof(ProductLds<RANKC_NT>) +
+                                               4 * (RANKC_NT / SPG_WAVE) + sizeof(RankItem)) + 64;
+struct RankShape {
+    int32_t RC, G;
+};
+__host__ __device__ inline RankShape rankc_shape(int64_t nr, int64_t cnnz, int32_t chunks, int32_t chunk_group, int32_t W,
+                                                 int64_t max_lds) {
+    auto group = [&](int64_t RC) {
+        int64_t G = cnnz > 0 ? (2 * RC * nr * chunks + cnnz) / (2 * cnnz) : chunks;
+        if (G > chunks) G = chunks;
+        if (G > chunk_group) G = chunk_group;
+        return G < 1 ? (int64_t)1 : G;
+    };
+    auto lds = [&](int64_t RC, int64_t G) { return RC * 8 + G * (W / 32) * 6 + RANKC_STATIC_LDS; };
+    int64_t RC = W > 4096 ? W : 4096;
+    int64_t G = group(RC);
+    while (G > 1 && lds(RC, G) > max_lds) --G;
+    int64_t wg = max_lds / lds(RC, G);  // workgroups per CU, at most 4 by their threads
+    if (wg < 1) wg = 1;
+    if (wg > 4) wg = 4;
+    constexpr int64_t STEP = 512;
+    while (G < chunks && G < chunk_group && RC + STEP < 65536 && lds(RC + STEP, group(RC + STEP)) * wg <= max_lds) {
+        RC += STEP;
+        G = group(RC);
+    }
+    return RankShape{(int32_t)RC, (int32_t)G};
 }
 
 // Work items of the rank-chunk bin, located on the device (counts of the
 // numeric classification): each row's chunks grouped greedily into items
 // of at most RC outputs and G chunks.
-__global__ void __launch_bounds__(256) k_rank_items(BinRef ref, const int32_t* heavy_idx, const int32_t* chunk_cnt,
-                                                    int32_t P, int32_t RC, int32_t chunk_group, int32_t W,
-                                                    int64_t static_lds, int64_t max_lds, const int64_t* cnnz_of_bin,
+__global__ void __launch_bounds__(256) k_rank_items(BinRef ref, const int64_t* a_beg, const int64_t* a_end,
+                                                    const int32_t* heavy_idx, const int32_t* chunk_cnt,
+                                                    int32_t P, int32_t chunk_group, int32_t W, int64_t max_lds,
+                                                    const int64_t* cnnz_of_bin,
                                                     RankItem* items, int32_t* nitems) {
     __shared__ int32_t tmp[256 / SPG_WAVE + 1];
     __shared__ int32_t s_base;
     const int32_t* rows;
     int64_t nrows;
     ref.locate(rows, nrows);
-    const int32_t G = rankc_group(nrows, *cnnz_of_bin, P, RC, chunk_group, W, static_lds, max_lds);
+    const RankShape shape = rankc_shape(nrows, *cnnz_of_bin, P, chunk_group, W, max_lds);
+    const int32_t RC = shape.RC, G = shape.G;
     for (int64_t r0 = (int64_t)blockIdx.x * 256; r0 < nrows; r0 += (int64_t)gridDim.x * 256) {
         const int64_t r = r0 + threadIdx.x;
-        const int32_t* cc = r < nrows ? chunk_cnt + (int64_t)heavy_idx[rows[r]] * P : nullptr;
+        const int32_t row = r < nrows ? rows[r] : 0;
+        const int32_t bslot = r < nrows ? heavy_idx[row] : 0;
+        const int32_t* cc = r < nrows ? chunk_cnt + (int64_t)bslot * P : nullptr;
+        const int64_t ab = r < nrows ? a_beg[row] : 0;
+        const int32_t an = r < nrows ? (int32_t)(a_end[row] - ab) : 0;
         // the greedy grouping of the row's chunks, walked twice: to count the
         // items (one global add per workgroup reserves their slots), then to
         // write them
@@ -708,76 +809,141 @@ __global__ void __launch_bounds__(256) k_rank_items(BinRef ref, const int32_t* h
         if (threadIdx.x == 0) s_base = total ? atomicAdd(nitems, total) : 0;
         __syncthreads();
         slot += s_base;
-        if (cc) walk([&](int c0, int c1, int32_t n, int64_t roff) { items[slot++] = RankItem{(int32_t)r, c0, c1, n, roff}; });
+        if (cc) walk([&](int c0, int c1, int32_t n, int64_t roff) { items[slot++] = RankItem{row, bslot, c0, c1, n, an, ab, roff}; });
         __syncthreads();
     }
 }
 
-// Dynamic LDS: G*W/32 packed words (prefix << 32 | bits), then RC values.
-template <int SR, int NT, int GM>
-__global__ void __launch_bounds__(NT) k_num_rankc(Csr A, Csr B, int32_t W, const int32_t* rows, const int64_t* a_beg,
-                                                  const int64_t* a_end, const uint32_t* bm_save,
-                                                  const int32_t* heavy_idx, int32_t nwords, const int32_t* split,
-                                                  int32_t P, const RankItem* items, const int32_t* nitems,
-                                                  int32_t RC, int32_t G, OutRows c_rp, int32_t* c_col,
-                                                  void* c_val) {
+// Dynamic LDS: RC values, then G*W/32 bitmap words and their 16-bit prefixes.
+// The item after the current one is fetched ahead: its bitmap words and the
+// A entries of its first batch are in registers, and the item after that on
+// its way to LDS, before the current item's products are gathered.
+// Bound by the traffic past L2 where B exceeds it and by latency elsewhere:
+// R-MAT scale 19 (7.6G products, B = 96 MB) 45.6 -> 27.2 ms alone at 6.4 TB/s
+// past L2 (copy rate 5.1); scale 16 (303M products) 1.13 -> 0.70 ms.  Before,
+// an item began with four dependent loads, its ranks with a serial walk over
+// LDS words, and each step that crossed segments with LDS reads; stores of C
+// that stayed in L2 displaced B (1.97 -> 1.91 ms for the scale-16 product).
+// Larger workgroups (768 and 1024 threads) gained nothing.
+// Workgroup b runs on XCD b mod 8; blocks of `run` consecutive items go to one
+// XCD, whose L2 then serves the lines that a row's items share (the ends of
+// their B segments, the split table).
+template <int SR, int NT, int GM, int KW>
+__global__ void __launch_bounds__(NT) k_num_rankc(Csr A, Csr B, int32_t W, const uint32_t* bm_save, int32_t nwords,
+                                                  const int32_t* split, int32_t P, const RankItem* items,
+                                                  const int32_t* nitems, int32_t run, int32_t RC, int32_t G, OutRows c_rp,
+                                                  int32_t* c_col, void* c_val) {
     typedef Sr<SR> S;
     typedef typename S::acc_t V;
     const int WPC = W / 32;  // bitmap words per chunk
     extern __shared__ uint64_t dyn[];
-    uint64_t* bw = dyn;
-    V* acc = reinterpret_cast<V*>(dyn + (int64_t)G * WPC);
-    __shared__ V s_av[NT];
+    V* acc = reinterpret_cast<V*>(dyn);                      // RC
+    uint32_t* bits = reinterpret_cast<uint32_t*>(acc + RC);  // G * WPC
+    uint16_t* pfx = reinterpret_cast<uint16_t*>(bits + G * WPC);
+    constexpr int EB = ProductLds<NT>::EB;
+    __shared__ V s_av[EB];
     __shared__ ProductLds<NT> L;
-    __shared__ int32_t red[NT / SPG_WAVE + 1];
-    for (int t = threadIdx.x; t < RC; t += NT) acc[t] = S::zero();
-    __syncthreads();
+    __shared__ int32_t tot[NT / SPG_WAVE];
+    __shared__ RankItem s_next;
+    constexpr int ITEM_WORDS = (int)(sizeof(RankItem) / 4);
+    const int wid = uniform32((int)(threadIdx.x / SPG_WAVE));
     const int32_t total_items = *nitems;
-    for (int32_t it = blockIdx.x; it < total_items; it += gridDim.x) {
-        const RankItem item = items[it];
-        const int64_t i = rows[item.r];
-        const uint32_t* src = bm_save + (int64_t)heavy_idx[i] * nwords + (int64_t)item.c0 * WPC;
-        // the last chunk of a row may be partial (n not a multiple of W): the
-        // saved bitmap ends at nwords, so stage no word past it (columns of
-        // the missing words are >= n and never looked up)
-        const int nw_full = (item.c1 - item.c0) * WPC, nw_left = nwords - item.c0 * WPC;
-        const int nw = nw_full < nw_left ? nw_full : nw_left;
-        const int64_t off = c_rp.off(i) + item.roff;
-        const int32_t cbase = item.c0 * W;
-        // packed words and columns
-        stage_bitmap_words<NT>(src, nw, bw);
-        __syncthreads();
-        pack_words_write_cols<NT>(bw, nw, cbase, item.cnt < RC ? item.cnt : RC, acc, c_col + off, red);
-        __syncthreads();
+    const int32_t xx = blockIdx.x & 7, xs = gridDim.x >> 3;
+    int32_t pos = blockIdx.x >> 3;
+    auto item_at = [&](int32_t q) { return (q / run * 8 + xx) * run + q % run; };
+    if (item_at(pos) >= total_items) return;
+    // the last chunk of a row may be partial (n not a multiple of W): the
+    // saved bitmap ends at nwords, so no word past it is read (columns of
+    // the missing words are >= n and never looked up)
+    auto words_of = [&](const RankItem& x) {
+        const int full = (x.c1 - x.c0) * WPC, left = nwords - x.c0 * WPC;
+        return full < left ? full : left;
+    };
+    auto bits_of = [&](const RankItem& x) { return bm_save + (int64_t)x.slot * nwords + (int64_t)x.c0 * WPC; };
+    uint32_t wv[KW];
+    int32_t ak = 0;
+    V av = S::zero();
+    int64_t noff = 0;
+    auto fetch = [&](const RankItem& x) {
+        fetch_words<NT, KW>(bits_of(x), words_of(x), wv);
+        ak = 0;
+        if ((int)threadIdx.x < x.annz) {
+            const int64_t p = x.a_beg + threadIdx.x;
+            ak = A.col[p];
+            av = S::load(A.val, p);
+        }
+        noff = c_rp.off(x.row);
+    };
+    // word t of the item at position q, in thread t (the first item where q is past the list)
+    auto item_word = [&](int32_t q) {
+        const int32_t it = item_at(q);
+        return (int)threadIdx.x < ITEM_WORDS
+                   ? reinterpret_cast<const int32_t*>(items + (it < total_items ? it : 0))[threadIdx.x]
+                   : 0;
+    };
+    auto put_item = [&](int32_t w) {
+        if ((int)threadIdx.x < ITEM_WORDS) reinterpret_cast<int32_t*>(&s_next)[threadIdx.x] = w;
+    };
+    RankItem item = uniform_item(items[item_at(pos)]);
+    fetch(item);
+    put_item(item_word(pos + xs));
+    __syncthreads();
+    while (true) {
         const int c0 = item.c0, c1 = item.c1;
+        const int32_t cnt = item.cnt < RC ? item.cnt : RC;
+        const int32_t cbase = c0 * W;
+        // B segment of an A entry: the B row's start, and the chunk range's
+        // ends inside it (one chunk covers all columns without a split table)
+        auto segment = [&](int64_t k, int64_t& rs, int64_t& lo, int64_t& hi) {
+            rs = B.rp[k];
+            if (split) {
+                lo = split[k * (P + 1) + c0];
+                hi = split[k * (P + 1) + c1];
+            } else {
+                lo = 0;
+                hi = B.rp[k + 1] - rs;
+            }
+        };
+        // loaded by whole waves (lanes without an entry: B row 0) and combined
+        // only after the bitmap's ranks are laid out
+        int64_t rs0 = 0, lo0 = 0, hi0 = 0;
+        if (wid * SPG_WAVE < item.annz) segment(ak, rs0, lo0, hi0);
+        const V av0 = av;
+        const int64_t off = uniform64(noff) + item.roff;
+        const RankItem next = uniform_item(s_next);
+        pos += xs;
+        const bool more = item_at(pos) < total_items;
+        rank_words<NT, KW>(bits_of(item), words_of(item), wv, bits, pfx, reinterpret_cast<int32_t*>(acc), cbase, tot);
+        __syncthreads();
+        write_staged_cols<NT>(acc, cnt, c_col + off);
+        if (more) fetch(next);
+        const int32_t nw = item_word(pos + xs);
+        __syncthreads();
+        const int64_t first_end = item.a_beg + EB;
         for_each_product_gm<NT, GM>(
-            a_beg[i], a_end[i], L,
+            item.a_beg, item.a_beg + item.annz, L,
             [&](int64_t p, int64_t& bs, int32_t& len) {
-                const int64_t k = A.col[p];
-                const int64_t rs = B.rp[k];
-                if (split) {
-                    const int32_t* sp = split + k * (P + 1);
-                    bs = rs + sp[c0];
-                    len = sp[c1] - sp[c0];
-                } else {  // one chunk covers all columns: the whole B row (no split table)
-                    bs = rs;
-                    len = (int32_t)(B.rp[k + 1] - rs);
-                }
+                int64_t rs = rs0, lo = lo0, hi = hi0;
+                if (p >= first_end) segment(A.col[p], rs, lo, hi);
+                bs = rs + lo;
+                len = (int32_t)(hi - lo);
             },
-            [&](int t, int64_t p) { s_av[t] = S::load(A.val, p); },
+            [&](int t, int64_t p) { s_av[t] = p < first_end ? av0 : S::load(A.val, p); },
             [&](int64_t q) { return BEntry<V>{B.col[q], S::load(B.val, q)}; },
             [&](int t, const BEntry<V>& x) {
                 const uint32_t j = (uint32_t)(x.col - cbase);
-                const uint64_t wd = bw[j >> 5];
-                const int32_t rank = (int32_t)(wd >> 32) + __popc((uint32_t)wd & ((1u << (j & 31)) - 1u));
-                if (rank < RC) S::lds_add(&acc[rank], S::mul(s_av[t], x.val));
+                const int32_t rank = (int32_t)pfx[j >> 5] + __popc(bits[j >> 5] & ((1u << (j & 31)) - 1u));
+                return BEntry<V>{rank, S::mul(s_av[t], x.val)};
+            },
+            [&](const BEntry<V>& y) {
+                if (y.col < RC) S::lds_add(&acc[y.col], y.val);
             });
-        const int32_t nout = item.cnt < RC ? item.cnt : RC;
-        for (int r = threadIdx.x; r < nout; r += NT) {
-            if (c_val) S::store(c_val, off + r, acc[r]);
-            acc[r] = S::zero();
-        }
+        if (c_val)
+            write_values<SR, NT>(acc, cnt, c_val, off);
+        if (!more) break;
+        put_item(nw);
         __syncthreads();
+        item = next;
     }
 }
 

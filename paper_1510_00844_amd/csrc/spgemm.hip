@@ -288,8 +288,6 @@ static inline unsigned rowinfo_grid(int64_t m) { return (unsigned)std::min<int64
 static const int RANK_STATIC_LDS = (int)(8 * 512 + sizeof(ProductLds<512>) + 4 * 16 + 256);
 static const int RANK_STATIC_LDS_1024 = (int)(8 * 1024 + sizeof(ProductLds<1024>) + 4 * 32 + 256);
 static int rank_static_lds(spg_plan P) { return P->opts.rank_block == 1024 ? RANK_STATIC_LDS_1024 : RANK_STATIC_LDS; }
-// rank-chunk items: at most this many outputs and this many column chunks
-static const int RANKC_CAP = 4096;
 // small counters and flags (int32), one size, never reallocated:
 //   [0]         long-row queue length (row analysis)
 //   [1, 17)     bin cursors of the symbolic classification
@@ -360,9 +358,12 @@ static void set_lds_attributes(spg_plan P) {
     hipFuncSetAttribute((const void*)k_num_rank<SR_F64, 1024, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank_1024);
     hipFuncSetAttribute((const void*)k_num_rank<SR_I64, 1024, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank_1024);
     hipFuncSetAttribute((const void*)k_num_rank<SR_BOOL, 1024, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank_1024);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
     hipFuncSetAttribute((const void*)k_learned_fused<SR_F64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
     hipFuncSetAttribute((const void*)k_learned_fused<SR_I64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
     hipFuncSetAttribute((const void*)k_learned_fused<SR_BOOL, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
@@ -373,9 +374,12 @@ static void set_lds_attributes_pipelined(spg_plan P) {
     const int dyn_bitmap = std::max(0, P->max_lds - (int)sizeof(ProductLds<512>) - 64 - 4 * MAX_CHUNKS);
     const int dyn_rank = std::max(0, P->max_lds - RANK_STATIC_LDS);
     hipFuncSetAttribute((const void*)k_sym_bitmap<512, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_bitmap);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, 512, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, 512, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, 512, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
 }
 
 static int gather_mode(int map, int unroll) { return (map == 2 ? 2 : 0) + (unroll == 8 ? 1 : 0); }
@@ -889,14 +893,6 @@ static spg_status read_counts(spg_plan P, const int64_t* c_row_ptr, int64_t m) {
     return SPG_OK;
 }
 
-// Items of the rank-chunk bin: RC outputs at most (at least one chunk).
-static int32_t rankc_capacity(spg_plan P) {
-    const int32_t W = P->opts.dense_chunk_cols;
-    int32_t RC = std::max(RANKC_CAP, W);
-    while (RC > W && (int64_t)(W / 32) * 8 + (int64_t)RC * 8 + RANK_STATIC_LDS > P->max_lds) RC /= 2;
-    return RC;
-}
-
 // Symbolic pass.  The bin kernels locate their rows on the device and stride
 // over them, so a launch is correct for any grid; the grids are sized from
 // the bin counts, read back once the first time these operands are seen and
@@ -1105,12 +1101,11 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
             const int32_t chunks = (int32_t)((b.ncols + W - 1) / W);
             SPG_TRY(P->rank_items.ensure(sizeof(RankItem) * (size_t)std::max<int64_t>(
                                              P->bm_cap * chunks, 1), "rank items"));
-            const int32_t RC = rankc_capacity(P);
             SPG_TRY(launch(P, "rank_items", [&] {
                 k_rank_items<<<(unsigned)std::min<int64_t>(grid_for(std::max<int64_t>(slots_used, 1), 256), 256), 256, 0,
                                cs(P)>>>(
-                    BinRef{nstats, lists, BIN_DENSE_PAR}, P->heavy_idx.as<int32_t>(),
-                    P->chunk_save.as<int32_t>(), chunks, RC, P->opts.chunk_group, W, RANK_STATIC_LDS, P->max_lds,
+                    BinRef{nstats, lists, BIN_DENSE_PAR}, P->a_beg.as<int64_t>(), P->a_end.as<int64_t>(),
+                    P->heavy_idx.as<int32_t>(), P->chunk_save.as<int32_t>(), chunks, P->opts.chunk_group, W, P->max_lds,
                     nstats + 3 * NBINS + BIN_DENSE_PAR, P->rank_items.as<RankItem>(), ctr + CTR_RANK_ITEMS);
             }));
         }
@@ -1221,40 +1216,50 @@ static spg_status numeric_sr(spg_plan P, Csr a, Csr b, const int64_t* c_row_ptr,
         } else if (bb >= BIN_RANK0) {
             const int32_t nwords = (int32_t)((b.ncols + 31) / 32);
             const int64_t cap = 4096ll << (bb - BIN_RANK0);
-            const size_t lds = (size_t)nwords * 8 + (size_t)cap * sizeof(typename Sr<SR>::acc_t);
+            const size_t lds = (size_t)nwords * 6 + (size_t)cap * sizeof(typename Sr<SR>::acc_t);
+            // 1024 threads where a CU holds only one workgroup of 512
+            const bool wide = P->opts.rank_block == 1024 || 2 * ((int64_t)lds + RANK_STATIC_LDS) > P->max_lds;
             SPG_TRY(with_gm(P, [&](auto gm) {
                 return launch(P, "num_rank" + std::to_string(cap), [&] {
-                    if (P->opts.rank_block == 1024)
+                    if (wide && (int64_t)lds + RANK_STATIC_LDS_1024 <= P->max_lds)
                         k_num_rank<SR, 1024, decltype(gm)::value><<<(unsigned)nr, 1024, lds, cs(P)>>>(
-                            a, b, rows, ab, ae, P->bm_save.as<uint32_t>(), P->heavy_idx.as<int32_t>(), nwords, crp,
-                            ccol, cval);
+                            a, b, rows, ab, ae, P->bm_save.as<uint32_t>(), P->heavy_idx.as<int32_t>(), nwords, (int32_t)cap,
+                            crp, ccol, cval);
                     else
                         k_num_rank<SR, 512, decltype(gm)::value><<<(unsigned)nr, 512, lds, cs(P)>>>(
-                            a, b, rows, ab, ae, P->bm_save.as<uint32_t>(), P->heavy_idx.as<int32_t>(), nwords, crp,
-                            ccol, cval);
+                            a, b, rows, ab, ae, P->bm_save.as<uint32_t>(), P->heavy_idx.as<int32_t>(), nwords, (int32_t)cap,
+                            crp, ccol, cval);
                 });
             }));
         } else if (bb == BIN_DENSE_PAR) {
             // items (formed in the symbolic pass) of at most RC outputs and G
             // chunks, G from the same rule as there
             const int32_t chunks = (int32_t)((b.ncols + W - 1) / W);
-            const int32_t RC = rankc_capacity(P);
-            const int32_t G = rankc_group(nr, P->num_counts[3 * NBINS + bb], chunks, RC, P->opts.chunk_group, W,
-                                          RANK_STATIC_LDS, P->max_lds);
+            const RankShape shape = rankc_shape(nr, P->num_counts[3 * NBINS + bb], chunks, P->opts.chunk_group, W,
+                                                P->max_lds);
+            const int32_t RC = shape.RC, G = shape.G;
             const int32_t* nitems = P->small_i32.as<int32_t>() + CTR_RANK_ITEMS;
             const int32_t nwords = (int32_t)((b.ncols + 31) / 32);
-            const size_t lds = (size_t)G * (W / 32) * 8 + (size_t)RC * sizeof(typename Sr<SR>::acc_t);
+            const size_t lds = (size_t)G * (W / 32) * 6 + (size_t)RC * sizeof(typename Sr<SR>::acc_t);
             const int32_t* split = chunks > 1 ? P->split.as<int32_t>() : nullptr;
-            const unsigned grid = (unsigned)std::min<int64_t>(nr * chunks, 256 * 8);
-            RankItem* items = P->rank_items.as<RankItem>();
-            const int32_t* hi = P->heavy_idx.as<int32_t>();
+            const unsigned grid = grid_for(std::min<int64_t>(nr * chunks, 256 * 8), 8) * 8;  // whole rounds of the XCDs
+            const RankItem* items = P->rank_items.as<RankItem>();
+            const uint32_t* bms = P->bm_save.as<uint32_t>();
+            // runs of items on one XCD pay where the gathers miss L2 (scale 19: 43.0 -> 42.0 ms; scale 16, whose
+            // B mostly hits, lost 1% with every run length tried)
+            const bool big = pipelined(P, b, 4 + (int64_t)sizeof(typename Sr<SR>::acc_t));
+            const int32_t run = big ? 16 : 1;
             SPG_TRY(with_gm_u<true>(P, P->opts.gather_map, P->opts.chunk_unroll, [&](auto gm) {
                 return launch(P, "num_rankc", [&] {
-                    k_num_rankc<SR, 512, decltype(gm)::value><<<grid, 512, lds, cs(P)>>>(
-                        a, b, W, rows, ab, ae, P->bm_save.as<uint32_t>(), hi, nwords, split, chunks, items, nitems, RC, G,
-                        crp, ccol, cval);
+                    // bitmap words held per thread: two cover items of few chunks with fewer registers
+                    if (G * (W / 32) <= 2 * RANKC_NT)
+                        k_num_rankc<SR, RANKC_NT, decltype(gm)::value, 2><<<grid, RANKC_NT, lds, cs(P)>>>(
+                            a, b, W, bms, nwords, split, chunks, items, nitems, run, RC, G, crp, ccol, cval);
+                    else
+                        k_num_rankc<SR, RANKC_NT, decltype(gm)::value, 8><<<grid, RANKC_NT, lds, cs(P)>>>(
+                            a, b, W, bms, nwords, split, chunks, items, nitems, run, RC, G, crp, ccol, cval);
                 });
-            }, pipelined(P, b, 4 + (int64_t)sizeof(typename Sr<SR>::acc_t))));
+            }, big));
         } else if (bb == BIN_DENSE) {
             const int32_t chunks = (int32_t)((b.ncols + W - 1) / W);
             P->dense_chunks = chunks;
