@@ -40,51 +40,63 @@ __device__ inline T group_reduce(T v, Op op) {
     return v;
 }
 
-__global__ void __launch_bounds__(256) k_mis_keys(int64_t n, const uint8_t* cand, uint64_t seed, int32_t round,
-                                                  uint64_t* key) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < n) key[v] = cand[v] ? mis_key(seed, round, v) : MIS_ABSENT;
-}
+// The four kernels of a round return at once when the round before left no
+// candidate (*live == 0), so rounds can be queued without reading the flag
+// back.  They are bound by the latency of the gathers; candidates are one byte
+// each and their keys are computed where they are read (a 64-bit mixer costs
+// less than gathering 8 bytes instead of 1), and rows whose result is settled
+// (no candidate) gather nothing.  7-point grid of 75^3 points, six rounds: the
+// last kernel 804 -> 25 us (it counted the remaining candidates with an atomic
+// per wave on one address; a flag is enough), the others 240 -> 165 us.
 
-// y(i) = min over stored A(i,j) of x(j)   (semiring (min, select2nd))
-__global__ void __launch_bounds__(256) k_mis_row_min(Csr A, const uint64_t* x, uint64_t* y) {
+// y(i) = min over stored A(i,j) of the candidates' keys x(j)   (semiring (min, select2nd))
+__global__ void __launch_bounds__(256) k_mis_row_min(Csr A, const uint8_t* cand, uint64_t seed, int32_t round,
+                                                     const int32_t* live, uint64_t* y) {
+    if (*live == 0) return;
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / MIS_LANES;
     const int gl = threadIdx.x % MIS_LANES;
     uint64_t m = MIS_ABSENT;
     if (i < A.nrows)
         for (int64_t p = A.rp[i] + gl; p < A.rp[i + 1]; p += MIS_LANES) {
-            const uint64_t t = x[A.col[p]];
-            m = t < m ? t : m;
+            const int64_t j = A.col[p];
+            if (cand[j]) {
+                const uint64_t t = mis_key(seed, round, j);
+                m = t < m ? t : m;
+            }
         }
     m = group_reduce(m, [](uint64_t a, uint64_t b) { return a < b ? a : b; });
     if (i < A.nrows && gl == 0) y[i] = m;
 }
 
 // Second hop and selection: minadj = min(m1(i), min over A(i,j) of m1(j));
-// a candidate whose key is not larger joins (newS) and stops being a
-// candidate.
-__global__ void __launch_bounds__(256) k_mis_select(Csr A, const uint64_t* key, const uint64_t* m1, uint8_t* cand,
-                                                    uint8_t* news) {
+// a candidate whose key is not larger joins (newS).  It stops being a
+// candidate in the pruning (the row minima of this round are read there no more).
+__global__ void __launch_bounds__(256) k_mis_select(Csr A, const uint8_t* cand, uint64_t seed, int32_t round,
+                                                    const int32_t* live, const uint64_t* m1, uint8_t* news) {
+    if (*live == 0) return;
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / MIS_LANES;
     const int gl = threadIdx.x % MIS_LANES;
+    const bool c = i < A.nrows && cand[i] != 0;
     uint64_t m = MIS_ABSENT;
-    if (i < A.nrows)
+    if (c)
         for (int64_t p = A.rp[i] + gl; p < A.rp[i + 1]; p += MIS_LANES) {
             const uint64_t t = m1[A.col[p]];
             m = t < m ? t : m;
         }
     m = group_reduce(m, [](uint64_t a, uint64_t b) { return a < b ? a : b; });
     if (i < A.nrows && gl == 0) {
-        const uint64_t mn = m1[i] < m ? m1[i] : m;
-        const bool c = cand[i] != 0;
-        const bool joins = c && key[i] <= mn;
+        bool joins = false;
+        if (c) {
+            const uint64_t mn = m1[i] < m ? m1[i] : m;
+            joins = mis_key(seed, round, i) <= mn;
+        }
         news[i] = joins ? 1 : 0;
-        if (joins) cand[i] = 0;
     }
 }
 
 // y(i) = OR over stored A(i,j) of x(j)
-__global__ void __launch_bounds__(256) k_mis_row_any(Csr A, const uint8_t* x, uint8_t* y) {
+__global__ void __launch_bounds__(256) k_mis_row_any(Csr A, const int32_t* live, const uint8_t* x, uint8_t* y) {
+    if (*live == 0) return;
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / MIS_LANES;
     const int gl = threadIdx.x % MIS_LANES;
     int hit = 0;
@@ -94,24 +106,27 @@ __global__ void __launch_bounds__(256) k_mis_row_any(Csr A, const uint8_t* x, ui
     if (i < A.nrows && gl == 0) y[i] = (uint8_t)hit;
 }
 
-// Second hop of the new vertices' neighbourhood, pruning of the candidates,
-// MIS-2 update, and the count of remaining candidates.
-__global__ void __launch_bounds__(256) k_mis_prune(Csr A, const uint8_t* a1, const uint8_t* news, uint8_t* cand,
-                                                   uint8_t* in_mis, int32_t* remaining) {
+// Second hop of the new vertices' neighbourhood, pruning of the candidates
+// (the new vertices among them), MIS-2 update, and *left = 1 when a candidate
+// remains.
+__global__ void __launch_bounds__(256) k_mis_prune(Csr A, const int32_t* live, const uint8_t* a1, const uint8_t* news,
+                                                   uint8_t* cand, uint8_t* in_mis, int32_t* left) {
+    if (*live == 0) return;
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / MIS_LANES;
     const int gl = threadIdx.x % MIS_LANES;
+    const bool c = i < A.nrows && cand[i] != 0;
     int hit = 0;
-    if (i < A.nrows)
+    if (c)
         for (int64_t p = A.rp[i] + gl; p < A.rp[i + 1] && !hit; p += MIS_LANES) hit = a1[A.col[p]] ? 1 : 0;
     hit = group_reduce(hit, [](int a, int b) { return a | b; });
-    bool left = false;
-    if (i < A.nrows && gl == 0) {
-        if (hit || a1[i]) cand[i] = 0;
-        if (news[i]) in_mis[i] = 1;
-        left = cand[i] != 0;
+    bool stays = false;
+    if (c && gl == 0) {
+        const bool joined = news[i] != 0;
+        if (joined) in_mis[i] = 1;
+        stays = !(joined || hit || a1[i]);
+        if (!stays) cand[i] = 0;
     }
-    const uint64_t b = __ballot(left);
-    if (lane_id() == 0 && b) atomicAdd(remaining, __popcll(b));
+    if (__ballot(stays) && lane_id() == 0) *left = 1;
 }
 
 // flags[v + 1] = in_mis(v), for the exclusive scan that numbers the roots
@@ -204,33 +219,50 @@ __global__ void __launch_bounds__(256) k_restrict_cols(int64_t n, const int32_t*
     }
 }
 
-// Sort each row's column indices (values are all equal): a wave per row,
-// register sort up to 64 entries, LDS sort up to 4096; *too_long counts rows
-// beyond that.
-__global__ void __launch_bounds__(64) k_sort_row_cols(int64_t nrows, const int64_t* rp, int32_t* col,
-                                                      int32_t* too_long) {
-    __shared__ uint64_t keys[4096];
-    const int64_t r = blockIdx.x;
+// Sort each row's column indices (values are all equal): rows of up to 64 by
+// a wave each in registers, four rows per workgroup and no LDS (with the LDS of
+// the longer rows in the same kernel only five waves fitted a CU: 53 -> 9 us
+// for 75^3 points).
+__global__ void __launch_bounds__(256) k_sort_row_cols(int64_t nrows, const int64_t* rp, int32_t* col) {
+    const int64_t r = (int64_t)blockIdx.x * 4 + threadIdx.x / SPG_WAVE;
     if (r >= nrows) return;
     const int64_t s = rp[r];
-    const int len = (int)(rp[r + 1] - s);
+    const int64_t len = rp[r + 1] - s;
+    if (len > SPG_WAVE) return;
     const int lane = lane_id();
-    if (len <= SPG_WAVE) {
-        uint64_t k = lane < len ? (uint64_t)(uint32_t)col[s + lane] : ~0ull;
-        k = wave_bitonic_sort_u64(k);
-        if (lane < len) col[s + lane] = (int32_t)k;
-        return;
+    const uint32_t k = wave_bitonic_sort_u32(lane < len ? (uint32_t)col[s + lane] : 0xffffffffu);
+    if (lane < len) col[s + lane] = (int32_t)k;
+}
+
+// The longer rows: a workgroup looks at 64 rows and sorts those of up to 4096
+// columns in LDS; *too_long counts rows beyond that.
+__global__ void __launch_bounds__(256) k_sort_long_row_cols(int64_t nrows, const int64_t* rp, int32_t* col,
+                                                            int32_t* too_long) {
+    __shared__ uint64_t keys[4096];
+    __shared__ uint64_t s_long;
+    const int64_t r0 = (int64_t)blockIdx.x * SPG_WAVE;
+    if (threadIdx.x < SPG_WAVE) {
+        const int64_t r = r0 + threadIdx.x;
+        const uint64_t m = __ballot(r < nrows && rp[r + 1] - rp[r] > SPG_WAVE);
+        if (threadIdx.x == 0) s_long = m;
     }
-    if (len > 4096) {
-        if (lane == 0) atomicAdd(too_long, 1);
-        return;
-    }
-    int P = 1;
-    while (P < len) P <<= 1;
-    for (int t = lane; t < P; t += SPG_WAVE) keys[t] = t < len ? (uint64_t)(uint32_t)col[s + t] : ~0ull;
     __syncthreads();
-    block_bitonic_sort_u64<SPG_WAVE>(keys, P);
-    for (int t = lane; t < len; t += SPG_WAVE) col[s + t] = (int32_t)keys[t];
+    for (uint64_t m = s_long; m; m &= m - 1) {
+        const int64_t r = r0 + __builtin_ctzll(m);
+        const int64_t s = rp[r];
+        const int64_t len = rp[r + 1] - s;
+        if (len > 4096) {
+            if (threadIdx.x == 0) atomicAdd(too_long, 1);
+            continue;
+        }
+        int P = 1;
+        while (P < len) P <<= 1;
+        for (int t = threadIdx.x; t < P; t += 256) keys[t] = t < len ? (uint64_t)(uint32_t)col[s + t] : ~0ull;
+        __syncthreads();
+        block_bitonic_sort_u64<256>(keys, P);
+        for (int t = threadIdx.x; t < len; t += 256) col[s + t] = (int32_t)keys[t];
+        __syncthreads();  // the row is done with the LDS
+    }
 }
 
 }  // namespace spg

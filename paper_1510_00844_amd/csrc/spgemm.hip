@@ -159,7 +159,7 @@ struct spg_plan_s {
     GalerkinState* galerkin = nullptr;
 
     // distance-2 independent sets and aggregation
-    DevBuf mis_key, mis_m1, mis_cand, mis_new, mis_a1, mis_flags, mis_agg1, mis_ctr;
+    DevBuf mis_m1, mis_cand, mis_new, mis_a1, mis_flags, mis_agg1, mis_ctr;
 
     // Sparse SUMMA stages (child plans created on first use)
     spg_plan summa_p = nullptr, summa_s = nullptr;
@@ -557,7 +557,7 @@ extern "C" spg_status spg_plan_destroy(spg_plan P) {
                       &P->lpt_hist, &P->lpt_tmp,
                       &P->lcap, &P->lcnt, &P->slot, &P->pcol, &P->pval, &P->fb_list, &P->fb_redo, &P->sub_rp,
                       &P->sub_col, &P->sub_val, &P->sub_crp, &P->mlp_tmp, &P->sub_pos,
-                      &P->mis_key, &P->mis_m1, &P->mis_cand, &P->mis_new, &P->mis_a1, &P->mis_flags, &P->mis_agg1,
+                      &P->mis_m1, &P->mis_cand, &P->mis_new, &P->mis_a1, &P->mis_flags, &P->mis_agg1,
                       &P->mis_ctr, &P->sm_pos, &P->sm_piece_rp, &P->sm_p_rp, &P->sm_p_col, &P->sm_p_val,
                       &P->sm_s_rp, &P->sm_s_col, &P->sm_s_val, &P->sm_c_rp, &P->sm_c_pos, &P->dc_pos})
         b->release();
@@ -2754,58 +2754,67 @@ extern "C" spg_status spg_mis2_aggregate(spg_plan P, const spg_csr* A, uint64_t 
     *n_agg = 0;
     if (n == 0) return SPG_OK;
     if (P->opts.validate) SPG_TRY(validate_csr(P, A, "A"));
-    SPG_TRY(P->mis_key.ensure(8 * (size_t)n, "MIS-2 keys"));
     SPG_TRY(P->mis_m1.ensure(8 * (size_t)n, "MIS-2 minima"));
     SPG_TRY(P->mis_cand.ensure((size_t)n, "MIS-2 candidates"));
     SPG_TRY(P->mis_new.ensure((size_t)n, "MIS-2 new vertices"));
     SPG_TRY(P->mis_a1.ensure((size_t)n, "MIS-2 neighbourhood"));
     SPG_TRY(P->mis_flags.ensure(8 * (size_t)(n + 1), "MIS-2 root numbers"));
     SPG_TRY(P->mis_agg1.ensure(4 * (size_t)n, "aggregates"));
-    SPG_TRY(P->mis_ctr.ensure(64, "counters"));
+    // flags: live[r] = 1 while round r has candidates; then the unassigned count
+    const int32_t nflags = MIS_MAX_ROUNDS + 2;
+    SPG_TRY(P->mis_ctr.ensure(sizeof(int32_t) * nflags, "counters"));
     Csr a = view(A);
     uint8_t* cand = P->mis_cand.as<uint8_t>();
     uint8_t* news = P->mis_new.as<uint8_t>();
     uint8_t* a1 = P->mis_a1.as<uint8_t>();
-    uint64_t* key = P->mis_key.as<uint64_t>();
     uint64_t* m1 = P->mis_m1.as<uint64_t>();
-    int32_t* ctr = P->mis_ctr.as<int32_t>();
+    int32_t* live = P->mis_ctr.as<int32_t>();
+    int32_t* unassigned = live + MIS_MAX_ROUNDS + 1;
     // fill kernels, not memsets (the sequence may be captured)
     auto fill_u8 = [&](uint8_t* p, uint8_t v) -> spg_status {
         return launch(P, "fill", [&] { k_fill_bytes<<<grid_for(n, 256), 256, 0, cs(P)>>>(p, n, v); });
     };
     SPG_TRY(fill_u8(cand, 1));
     SPG_TRY(fill_u8(in_mis, 0));
-    int32_t r = 0;
-    for (;; ++r) {
+    SPG_TRY(fill_i32(P, live, 1, 1));
+    SPG_TRY(fill_i32(P, live + 1, nflags - 1, 0));
+    // rounds are queued four at a time before the flags are read back (the
+    // kernels of a round without candidates return at once)
+    int32_t r = 0, used = -1;
+    std::vector<int32_t> h_live(nflags);
+    while (used < 0) {
         if (r >= MIS_MAX_ROUNDS) return fail(SPG_ERR_STATE, "MIS-2 did not finish (pattern not symmetric?)");
-        SPG_TRY(fill_i32(P, ctr, 1, 0));
-        SPG_TRY(launch(P, "mis_keys", [&] {
-            k_mis_keys<<<grid_for(n, 256), 256, 0, cs(P)>>>(n, cand, seed, r, key);
-        }));
-        SPG_TRY(launch(P, "mis_row_min", [&] { k_mis_row_min<<<grid_rows(n), 256, 0, cs(P)>>>(a, key, m1); }));
-        SPG_TRY(launch(P, "mis_select", [&] { k_mis_select<<<grid_rows(n), 256, 0, cs(P)>>>(a, key, m1, cand, news); }));
-        SPG_TRY(launch(P, "mis_row_any", [&] { k_mis_row_any<<<grid_rows(n), 256, 0, cs(P)>>>(a, news, a1); }));
-        SPG_TRY(launch(P, "mis_prune", [&] {
-            k_mis_prune<<<grid_rows(n), 256, 0, cs(P)>>>(a, a1, news, cand, in_mis, ctr);
-        }));
-        int32_t left = 0;
-        HIP_TRY(hipMemcpyAsync(&left, ctr, sizeof(int32_t), hipMemcpyDeviceToHost, P->stream));
+        const int32_t r0 = r, r1 = std::min(r + 4, (int32_t)MIS_MAX_ROUNDS);
+        for (; r < r1; ++r) {
+            const int32_t* lv = live + r;
+            SPG_TRY(launch(P, "mis_row_min", [&] {
+                k_mis_row_min<<<grid_rows(n), 256, 0, cs(P)>>>(a, cand, seed, r, lv, m1);
+            }));
+            SPG_TRY(launch(P, "mis_select", [&] {
+                k_mis_select<<<grid_rows(n), 256, 0, cs(P)>>>(a, cand, seed, r, lv, m1, news);
+            }));
+            SPG_TRY(launch(P, "mis_row_any", [&] { k_mis_row_any<<<grid_rows(n), 256, 0, cs(P)>>>(a, lv, news, a1); }));
+            SPG_TRY(launch(P, "mis_prune", [&] {
+                k_mis_prune<<<grid_rows(n), 256, 0, cs(P)>>>(a, lv, a1, news, cand, in_mis, live + r + 1);
+            }));
+        }
+        HIP_TRY(hipMemcpyAsync(h_live.data(), live, sizeof(int32_t) * (r1 + 1), hipMemcpyDeviceToHost, P->stream));
         HIP_TRY(hipStreamSynchronize(P->stream));
-        if (left == 0) break;
+        for (int32_t x = r0; x < r1 && used < 0; ++x)
+            if (h_live[x + 1] == 0) used = x + 1;
     }
-    if (rounds) *rounds = r + 1;
+    if (rounds) *rounds = used;
     // aggregates: roots numbered in vertex order, then their neighbours, then the rest
     int64_t* flags = P->mis_flags.as<int64_t>();
     SPG_TRY(launch(P, "mis_flags", [&] { k_mis_flags<<<grid_for(n, 256), 256, 0, cs(P)>>>(n, in_mis, flags); }));
     SPG_TRY(scan_counts(P, flags, n));
     int32_t* agg1 = P->mis_agg1.as<int32_t>();
     SPG_TRY(launch(P, "agg_roots", [&] { k_agg_roots<<<grid_rows(n), 256, 0, cs(P)>>>(a, in_mis, flags, agg1); }));
-    SPG_TRY(fill_i32(P, ctr + 1, 1, 0));
-    SPG_TRY(launch(P, "agg_rest", [&] { k_agg_rest<<<grid_rows(n), 256, 0, cs(P)>>>(a, agg1, seed, agg, ctr + 1); }));
+    SPG_TRY(launch(P, "agg_rest", [&] { k_agg_rest<<<grid_rows(n), 256, 0, cs(P)>>>(a, agg1, seed, agg, unassigned); }));
     int64_t h[2] = {0, 0};
     int32_t un = 0;
     HIP_TRY(hipMemcpyAsync(&h[0], flags + n, sizeof(int64_t), hipMemcpyDeviceToHost, P->stream));
-    HIP_TRY(hipMemcpyAsync(&un, ctr + 1, sizeof(int32_t), hipMemcpyDeviceToHost, P->stream));
+    HIP_TRY(hipMemcpyAsync(&un, unassigned, sizeof(int32_t), hipMemcpyDeviceToHost, P->stream));
     HIP_TRY(hipStreamSynchronize(P->stream));
     if (un) return fail(SPG_ERR_STATE, "some vertices are farther than two hops from the independent set");
     *n_agg = h[0];
@@ -2831,7 +2840,10 @@ static spg_status restriction_sr(spg_plan P, int64_t n, int64_t na, const int32_
     int32_t* ctr = P->mis_ctr.as<int32_t>();
     SPG_TRY(fill_i32(P, ctr + 2, 1, 0));
     SPG_TRY(launch(P, "sort_row_cols", [&] {
-        k_sort_row_cols<<<(unsigned)na, 64, 0, cs(P)>>>(na, rt_rp, rt_col, ctr + 2);
+        k_sort_row_cols<<<grid_for(na, 4), 256, 0, cs(P)>>>(na, rt_rp, rt_col);
+    }));
+    SPG_TRY(launch(P, "sort_row_cols", [&] {
+        k_sort_long_row_cols<<<grid_for(na, SPG_WAVE), 256, 0, cs(P)>>>(na, rt_rp, rt_col, ctr + 2);
     }));
     int32_t bad = 0;
     HIP_TRY(hipMemcpyAsync(&bad, ctr + 2, sizeof(int32_t), hipMemcpyDeviceToHost, P->stream));

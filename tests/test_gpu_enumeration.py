@@ -87,3 +87,19 @@ def test_enumeration_special_values(opts):
         assert torch.equal(torch.isnan(got), torch.isnan(ref))
         assert torch.equal(torch.isinf(got), torch.isinf(ref))
     plan.close()
+
+
+@pytest.mark.parametrize("sizes", [[64, 65, 1, 63], [4096, 2, 65], [1000] * 3 + [1] * 70 + [129], [1]])
+def test_restriction_row_lengths(sizes):
+    """R^T rows around the register sort's 64 and up to the LDS sort's 4096."""
+    rng = np.random.default_rng(1)
+    agg = rng.permutation(np.repeat(np.arange(len(sizes)), sizes)).astype(np.int32)
+    plan = spg.Plan()
+    R, RT = spg.spg_restriction(plan, "i64", torch.from_numpy(agg).cuda(), len(sizes))
+    order = np.argsort(agg, kind="stable")
+    assert np.array_equal(RT.row_ptr.cpu().numpy(), np.concatenate([[0], np.cumsum(sizes)]))
+    assert np.array_equal(RT.col.cpu().numpy(), order)
+    assert np.array_equal(R.col.cpu().numpy(), agg)
+    with pytest.raises(spg.SpgError):
+        spg.spg_restriction(plan, "i64", torch.zeros(4097, dtype=torch.int32, device="cuda"), 1)
+    plan.close()
