@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(256) k_learned_classify(int64_t m, int64_t n, 
                                                           LearnedParams lp, BinParams bp, const int64_t* a_beg,
                                                           const int64_t* a_end, const int64_t* flops,
                                                           const int32_t* maxb, uint8_t* bin, int64_t* cap,
-                                                          int64_t* cnt, int64_t* bin_stats) {
+                                                          int64_t* cnt, int64_t* bin_stats, OrderedBins order) {
     __shared__ float s_p[MLP_NPARAMS];
     __shared__ int s_hist[NBINS];
     __shared__ int64_t s_flops[NBINS];
@@ -111,6 +111,7 @@ __global__ void __launch_bounds__(256) k_learned_classify(int64_t m, int64_t n, 
         }
         bin[i] = (uint8_t)b;
         cap[i] = b == BIN_DENSE ? 0 : c;  // exact-method rows get no slot
+        if (order.has(b)) atomicAdd(&order.hist[order.key(b, f)], 1);  // fused rows: heaviest first
         atomicAdd(&s_hist[b], 1);
         atomicAdd((unsigned long long*)&s_flops[b], (unsigned long long)f);
     }

@@ -785,22 +785,31 @@ __global__ void __launch_bounds__(256) k_rank_items(BinRef ref, const int64_t* a
         const int32_t an = r < nrows ? (int32_t)(a_end[row] - ab) : 0;
         // the greedy grouping of the row's chunks, walked twice: to count the
         // items (one global add per workgroup reserves their slots), then to
-        // write them
+        // write them; eight counts are loaded before any is looked at
         auto walk = [&](auto emit) {
             int64_t roff = 0;
             int c0 = 0;
-            while (c0 < P) {
-                int c1 = c0;
-                int32_t n = 0;
-                while (c1 < P && c1 - c0 < G && n + cc[c1] <= RC) n += cc[c1++];
-                if (c1 == c0) {  // a chunk above RC (the host keeps RC >= W): take it alone, always progress
-                    n = cc[c0];
-                    c1 = c0 + 1;
-                }
+            int32_t n = 0;  // outputs of chunks [c0, c)
+            auto close = [&](int c1) {
                 if (n > 0) emit(c0, c1, n, roff);
                 roff += n;
+                n = 0;
                 c0 = c1;
+            };
+            for (int cb = 0; cb < P; cb += 8) {
+                int32_t v[8];
+#pragma unroll
+                for (int x = 0; x < 8; ++x) v[x] = cb + x < P ? cc[cb + x] : 0;
+#pragma unroll
+                for (int x = 0; x < 8; ++x) {
+                    const int c = cb + x;
+                    if (c >= P) break;
+                    // (the host keeps RC >= W, so a chunk alone always fits)
+                    if (c > c0 && (c - c0 >= G || n + v[x] > RC)) close(c);
+                    n += v[x];
+                }
             }
+            close(P);
         };
         int32_t mine = 0;
         if (cc) walk([&](int, int, int32_t, int64_t) { ++mine; });

@@ -6,8 +6,9 @@
 //   flops[i]            sum over those entries k of nnz(B(k,:))
 //   maxb[i]             max over those k of nnz(B(k,:))  (a lower bound of nnz(C(i,:)))
 //   bin[i]              the accumulator class the row is sent to
-// Rows with at most LONG_ROW entries are handled by 16-lane groups; longer
-// rows are queued for a workgroup each so no wave walks a hub row alone.
+// Rows with at most LONG_ROW entries are handled by 16-lane groups, longer ones
+// by a wave and those above HUB_ROW by their whole workgroup, so no wave walks
+// a hub row alone.
 #pragma once
 #include "common.hpp"
 
@@ -32,7 +33,7 @@ constexpr int BIN_DENSE_PAR = 11;  // numeric: column chunks of one row in paral
 constexpr int BIN_RANK0 = 13;  // rank-space accumulator, capacity 4096 << (b - BIN_RANK0)
 constexpr int BIN_HEAP = 16;   // k-way merge of the row's few B rows (both passes)
 constexpr int RANK_MIN_LOG2 = 12;
-constexpr int LONG_ROW = 128;
+constexpr int LONG_ROW = 128, HUB_ROW = 2048;
 constexpr int HASH_MIN_LOG2 = 7;  // 128 slots
 
 __device__ inline int ceil_log2_i64(int64_t x) {
@@ -113,6 +114,31 @@ __device__ inline void for_each_bin_row(const BinRef& ref, Body body) {
     }
 }
 
+// Longest-processing-time order of the row lists of a run of consecutive
+// bins [b_lo, b_hi): within each bin, rows with more products first, so that
+// the heaviest workgroups start early and the end of a launch is not held up
+// by a large row that started last.  The classification counts the rows of
+// those bins by (bin, work class) and the scatter places them by it; 256 work
+// classes per bin, 8 per power of two of the products (rows within about 12%
+// of each other share a class).
+constexpr int LPT_KEYS = 256;
+constexpr int LPT_MAX_BINS = 5;
+__device__ inline int lpt_class(int64_t w) {
+    if (w < 1) w = 1;
+    const int e = 63 - __clzll((unsigned long long)w);  // floor(log2 w)
+    const int frac = e >= 3 ? (int)((w >> (e - 3)) & 7) : (int)((w << (3 - e)) & 7);
+    const int k = e * 8 + frac;
+    return LPT_KEYS - 1 - (k < LPT_KEYS - 1 ? k : LPT_KEYS - 1);  // more work: smaller class
+}
+struct OrderedBins {
+    int32_t b_lo, b_hi;  // none when equal
+    int32_t* hist;       // rows by key, (b_hi - b_lo) LPT_KEYS of them
+    const int64_t* work;
+    __host__ __device__ bool has(int b) const { return b >= b_lo && b < b_hi; }
+    __device__ int key(int b, int64_t w) const { return (b - b_lo) * LPT_KEYS + lpt_class(w); }
+    __host__ __device__ int keys() const { return (b_hi - b_lo) * LPT_KEYS; }
+};
+
 struct RowInfoOut {
     int64_t* a_beg;
     int64_t* a_end;
@@ -121,9 +147,8 @@ struct RowInfoOut {
     uint8_t* bin;
     int64_t* cnt;        // symbolic counts (c_row_ptr + 1); EMPTY/TINY rows written here
     int64_t* bin_stats;  // [3][NBINS]: rows, flops, A entries
-    int32_t* long_rows;  // queue of rows with more than LONG_ROW entries
-    int32_t* long_count;
     unsigned long long* max_flops;  // largest flops_i over the rows (one value)
+    OrderedBins order;
 };
 
 __device__ inline int64_t lower_bound_col(const int32_t* col, int64_t lo, int64_t hi, int64_t key) {
@@ -134,9 +159,41 @@ __device__ inline int64_t lower_bound_col(const int32_t* col, int64_t lo, int64_
     return lo;
 }
 
+// Per-workgroup statistics of a classification, added to the global ones once.
+// Device-wide atomics on a few addresses serialize across the XCDs (about 2 ns
+// each), so the classification grids are kept to few, large workgroups.
+constexpr int CLASS_NT = 1024;
+template <int NV>
+struct ClassLds {
+    int32_t rows[NBINS];
+    unsigned long long v[NV][NBINS];
+    unsigned long long fmax;
+    int32_t lpt[LPT_KEYS * LPT_MAX_BINS];
+
+    __device__ void clear(const OrderedBins& o) {
+        if (threadIdx.x < NBINS) {
+            rows[threadIdx.x] = 0;
+            for (int x = 0; x < NV; ++x) v[x][threadIdx.x] = 0;
+        }
+        if (threadIdx.x == 0) fmax = 0;
+        for (int k = threadIdx.x; k < o.keys(); k += CLASS_NT) lpt[k] = 0;
+        __syncthreads();
+    }
+    __device__ void flush(const OrderedBins& o, int64_t* stats, unsigned long long* max_flops) {
+        __syncthreads();
+        if (threadIdx.x < NBINS && rows[threadIdx.x]) {
+            const int b = threadIdx.x;
+            atomicAdd((unsigned long long*)&stats[b], (unsigned long long)rows[b]);
+            for (int x = 0; x < NV; ++x) atomicAdd((unsigned long long*)&stats[(x + 1) * NBINS + b], v[x][b]);
+        }
+        if (max_flops && threadIdx.x == 0 && fmax) atomicMax(max_flops, fmax);
+        for (int k = threadIdx.x; k < o.keys(); k += CLASS_NT)
+            if (lpt[k]) atomicAdd(&o.hist[k], lpt[k]);
+    }
+};
+
 __device__ inline void finish_row(int64_t i, int64_t beg, int64_t end, int64_t f, int32_t mb,
-                                  const BinParams& bp, const RowInfoOut& o, int* s_hist,
-                                  int64_t* s_flops, int64_t* s_annz, unsigned long long* s_fmax) {
+                                  const BinParams& bp, const RowInfoOut& o, ClassLds<2>& c) {
     o.a_beg[i] = beg;
     o.a_end[i] = end;
     o.flops[i] = f;
@@ -145,313 +202,294 @@ __device__ inline void finish_row(int64_t i, int64_t beg, int64_t end, int64_t f
     o.bin[i] = (uint8_t)b;
     if (b == BIN_EMPTY) o.cnt[i] = 0;
     else if (b == BIN_TINY) o.cnt[i] = f;  // nnz(C(i,:)) = nnz(B(k,:)) exactly
-    atomicAdd(&s_hist[b], 1);
-    atomicAdd((unsigned long long*)&s_flops[b], (unsigned long long)f);
-    atomicAdd((unsigned long long*)&s_annz[b], (unsigned long long)(end - beg));
-    atomicMax(s_fmax, (unsigned long long)f);
+    atomicAdd(&c.rows[b], 1);
+    atomicAdd(&c.v[0][b], (unsigned long long)f);
+    atomicAdd(&c.v[1][b], (unsigned long long)(end - beg));
+    if (o.order.has(b)) atomicAdd(&c.lpt[o.order.key(b, f)], 1);
 }
 
-__device__ inline void flush_stats(const RowInfoOut& o, int* s_hist, int64_t* s_flops,
-                                   int64_t* s_annz, unsigned long long* s_fmax) {
-    if (threadIdx.x == 0 && *s_fmax) atomicMax(o.max_flops, *s_fmax);
-    if (threadIdx.x < NBINS) {
-        int b = threadIdx.x;
-        if (s_hist[b]) {
-            atomicAdd((unsigned long long*)&o.bin_stats[b], (unsigned long long)s_hist[b]);
-            atomicAdd((unsigned long long*)&o.bin_stats[NBINS + b], (unsigned long long)s_flops[b]);
-            atomicAdd((unsigned long long*)&o.bin_stats[2 * NBINS + b], (unsigned long long)s_annz[b]);
-        }
-    }
-}
-
-__device__ inline void rowinfo_row(const Csr& A, const Csr& B, int64_t k_lo, int64_t k_hi, int full_window,
-                                   const BinParams& bp, const RowInfoOut& o, int64_t i, int gl, int* s_hist,
-                                   int64_t* s_flops, int64_t* s_annz, unsigned long long* s_fmax);
-
-// 256 threads = 16 groups of 16 lanes, one row per group; the grid strides
-// over groups of 16 rows (few workgroups, so few global statistics atomics).
-__global__ void __launch_bounds__(256) k_rowinfo(Csr A, Csr B, int64_t k_lo, int64_t k_hi,
-                                                 int full_window, BinParams bp, RowInfoOut o) {
-    __shared__ int s_hist[NBINS];
-    __shared__ int64_t s_flops[NBINS], s_annz[NBINS];
-    __shared__ unsigned long long s_fmax;
-    if (threadIdx.x < NBINS) {
-        s_hist[threadIdx.x] = 0;
-        s_flops[threadIdx.x] = 0;
-        s_annz[threadIdx.x] = 0;
-    }
-    if (threadIdx.x == 0) s_fmax = 0;
-    __syncthreads();
-    const int g = threadIdx.x >> 4, gl = threadIdx.x & 15;
-    for (int64_t i0 = (int64_t)blockIdx.x * 16; i0 < A.nrows; i0 += (int64_t)gridDim.x * 16)
-        rowinfo_row(A, B, k_lo, k_hi, full_window, bp, o, i0 + g, gl, s_hist, s_flops, s_annz, &s_fmax);
-    __syncthreads();
-    flush_stats(o, s_hist, s_flops, s_annz, &s_fmax);
-}
-
-__device__ inline void rowinfo_row(const Csr& A, const Csr& B, int64_t k_lo, int64_t k_hi, int full_window,
-                                   const BinParams& bp, const RowInfoOut& o, int64_t i, int gl, int* s_hist,
-                                   int64_t* s_flops, int64_t* s_annz, unsigned long long* s_fmax) {
-    bool active = i < A.nrows;
-    int64_t beg = 0, end = 0;
-    if (active) {
-        beg = A.rp[i];
-        end = A.rp[i + 1];
-        if (!full_window) {
-            // the A row is sorted by column: binary search the window edges
-            beg = lower_bound_col(A.col, beg, end, k_lo);
-            end = lower_bound_col(A.col, beg, end, k_hi);
-        }
-        if (end - beg > LONG_ROW) {
-            if (gl == 0) {
-                int slot = atomicAdd(o.long_count, 1);
-                o.long_rows[slot] = (int32_t)i;
-            }
-            active = false;
-        }
-    }
-    int64_t f = 0;
-    int32_t mb = 0;
-    if (active) {
-        // two A entries per lane per step, so their dependent loads overlap
-        for (int64_t p = beg + gl; p < end; p += 32) {
-            const bool two = p + 16 < end;
-            const int64_t k0 = A.col[p];
-            const int64_t k1 = two ? (int64_t)A.col[p + 16] : k0;
-            const int64_t l0 = B.rp[k0 + 1] - B.rp[k0];
-            const int64_t l1 = two ? B.rp[k1 + 1] - B.rp[k1] : 0;
-            f += l0 + l1;
-            mb = l0 > mb ? (int32_t)l0 : mb;
-            mb = l1 > mb ? (int32_t)l1 : mb;
-        }
-    }
-    // reduce inside the 16-lane group (xor offsets < 16 stay in the group)
+// Products and longest B row of A's entries lb + t, lb + t + stride, ... < le, four in flight.
+__device__ inline void walk_entries(const Csr& A, const Csr& B, int64_t lb, int64_t le, int t, int stride, int64_t& f,
+                                    int32_t& mb) {
+    constexpr int U = 4;
+    f = 0;
+    mb = 0;
+    for (int64_t p0 = lb + t; p0 < le; p0 += U * stride) {
+        int64_t k[U], l[U];
 #pragma unroll
-    for (int d = 8; d > 0; d >>= 1) {
-        f += __shfl_xor(f, d, SPG_WAVE);
-        int32_t o2 = __shfl_xor(mb, d, SPG_WAVE);
-        mb = o2 > mb ? o2 : mb;
+        for (int u = 0; u < U; ++u) k[u] = p0 + u * stride < le ? (int64_t)A.col[p0 + u * stride] : -1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) l[u] = k[u] >= 0 ? B.rp[k[u] + 1] - B.rp[k[u]] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            f += l[u];
+            mb = l[u] > mb ? (int32_t)l[u] : mb;
+        }
     }
-    if (active && gl == 0) finish_row(i, beg, end, f, mb, bp, o, s_hist, s_flops, s_annz, s_fmax);
 }
 
-// One 256-thread workgroup per queued long row, grid-stride over the queue.
-__global__ void __launch_bounds__(256) k_rowinfo_long(Csr A, Csr B, int64_t k_lo, int64_t k_hi,
-                                                      int full_window, BinParams bp,
-                                                      RowInfoOut o) {
-    __shared__ int s_hist[NBINS];
-    __shared__ int64_t s_flops[NBINS], s_annz[NBINS];
-    __shared__ int64_t s_red[8];
-    __shared__ int32_t s_redm[8];
-    __shared__ unsigned long long s_fmax;
-    if (threadIdx.x < NBINS) {
-        s_hist[threadIdx.x] = 0;
-        s_flops[threadIdx.x] = 0;
-        s_annz[threadIdx.x] = 0;
+// 1024 threads = 64 groups of 16 lanes; a group takes two rows at a time, so
+// that the dependent loads (row extent, A columns, B row extents) of both are
+// in flight together.  Bound by that latency: at most 512 workgroups (every
+// wave slot once, few statistics atomics), no barrier in the loop.
+__global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo, int64_t k_hi,
+                                                      int full_window, BinParams bp, RowInfoOut o) {
+    constexpr int G = 16, NG = CLASS_NT / G, R = 2, E = 2;  // lanes a row, groups, rows a group, entries a lane
+    constexpr int HUBS = 512;
+    __shared__ ClassLds<2> c;
+    __shared__ int32_t s_hub[HUBS];
+    __shared__ int32_t s_nhub;
+    __shared__ int64_t s_f[CLASS_NT / SPG_WAVE];
+    __shared__ int32_t s_mb[CLASS_NT / SPG_WAVE];
+    if (threadIdx.x == 0) s_nhub = 0;
+    c.clear(o.order);
+    const int g = threadIdx.x / G, gl = threadIdx.x % G, lane = lane_id();
+    unsigned long long fmax = 0;
+    auto finish = [&](int64_t i, int64_t beg, int64_t end, int64_t f, int32_t mb) {
+        finish_row(i, beg, end, f, mb, bp, o, c);
+        fmax = (unsigned long long)f > fmax ? (unsigned long long)f : fmax;
+    };
+    auto window = [&](int64_t& beg, int64_t& end) {
+        if (full_window) return;
+        // the A row is sorted by column: binary search the window edges
+        beg = lower_bound_col(A.col, beg, end, k_lo);
+        end = lower_bound_col(A.col, beg, end, k_hi);
+    };
+    const int64_t step = (int64_t)gridDim.x * NG;
+    for (int64_t i0 = (int64_t)blockIdx.x * NG; i0 < A.nrows; i0 += R * step) {
+        int64_t beg[R], end[R], f[R];
+        int32_t mb[R];
+        bool active[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int64_t i = i0 + u * step + g;
+            active[u] = i < A.nrows;
+            beg[u] = active[u] ? A.rp[i] : 0;
+            end[u] = active[u] ? A.rp[i + 1] : 0;
+            f[u] = 0;
+            mb[u] = 0;
+        }
+        uint64_t longs[R];  // the wave's groups with a long row (a bit per lane of them)
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            if (active[u]) window(beg[u], end[u]);
+            const bool is_long = end[u] - beg[u] > LONG_ROW;
+            bool hub = false;
+            if (is_long && gl == 0 && end[u] - beg[u] > HUB_ROW) {
+                const int slot = atomicAdd(&s_nhub, 1);
+                if (slot < HUBS) {  // (past the queue's end: by the wave)
+                    s_hub[slot] = (int32_t)(i0 + u * step + g);
+                    hub = true;
+                }
+            }
+            longs[u] = __builtin_amdgcn_ballot_w64(is_long && gl == 0 && !hub);
+            if (is_long) active[u] = false;
+        }
+        int64_t most = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) most = active[u] && end[u] - beg[u] > most ? end[u] - beg[u] : most;
+        for (int64_t x = gl; x < most; x += G * E) {
+            int64_t k[R][E], l0[R][E], l1[R][E];
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int64_t p = beg[u] + x + e * G;
+                    k[u][e] = active[u] && p < end[u] ? (int64_t)A.col[p] : -1;
+                }
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    l0[u][e] = k[u][e] >= 0 ? B.rp[k[u][e]] : 0;
+                    l1[u][e] = k[u][e] >= 0 ? B.rp[k[u][e] + 1] : 0;
+                }
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int64_t l = l1[u][e] - l0[u][e];
+                    f[u] += l;
+                    mb[u] = l > mb[u] ? (int32_t)l : mb[u];
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            // reduce inside the 16-lane group (xor offsets < 16 stay in the group)
+#pragma unroll
+            for (int d = G / 2; d > 0; d >>= 1) {
+                f[u] += lane_xor(f[u], d);
+                const int32_t o2 = lane_xor(mb[u], d);
+                mb[u] = o2 > mb[u] ? o2 : mb[u];
+            }
+            if (active[u] && gl == 0) finish(i0 + u * step + g, beg[u], end[u], f[u], mb[u]);
+            for (uint64_t m = longs[u]; m; m &= m - 1) {
+                const int l = __builtin_ctzll(m);
+                const int64_t lb = lane_get(beg[u], l), le = lane_get(end[u], l);
+                int64_t lf;
+                int32_t lm;
+                walk_entries(A, B, lb, le, lane, SPG_WAVE, lf, lm);
+                lf = wave_reduce_add(lf);
+                lm = wave_reduce_max(lm);
+                if (lane == l) finish(i0 + u * step + g, lb, le, lf, lm);
+            }
+        }
     }
-    if (threadIdx.x == 0) s_fmax = 0;
     __syncthreads();
-    const int nq = *o.long_count;
-    for (int q = blockIdx.x; q < nq; q += gridDim.x) {
-        const int64_t i = o.long_rows[q];
-        int64_t beg = A.rp[i], end = A.rp[i + 1];
-        if (!full_window) {
-            beg = lower_bound_col(A.col, beg, end, k_lo);
-            end = lower_bound_col(A.col, beg, end, k_hi);
-        }
-        int64_t f = 0;
-        int32_t mb = 0;
-        for (int64_t p = beg + threadIdx.x; p < end; p += 256) {
-            int64_t k = A.col[p];
-            int64_t len = B.rp[k + 1] - B.rp[k];
-            f += len;
-            mb = len > mb ? (int32_t)len : mb;
-        }
-        f = wave_reduce_add(f);
-        mb = wave_reduce_max(mb);
+    const int nhub = s_nhub < HUBS ? s_nhub : HUBS;
+    for (int q = 0; q < nhub; ++q) {
+        const int64_t i = s_hub[q];
+        int64_t lb = A.rp[i], le = A.rp[i + 1];
+        window(lb, le);
+        int64_t lf;
+        int32_t lm;
+        walk_entries(A, B, lb, le, threadIdx.x, CLASS_NT, lf, lm);
+        lf = wave_reduce_add(lf);
+        lm = wave_reduce_max(lm);
         const int w = threadIdx.x / SPG_WAVE;
-        if (lane_id() == 0) {
-            s_red[w] = f;
-            s_redm[w] = mb;
+        if (lane == 0) {
+            s_f[w] = lf;
+            s_mb[w] = lm;
         }
         __syncthreads();
         if (threadIdx.x == 0) {
             int64_t tf = 0;
             int32_t tm = 0;
-            for (int x = 0; x < 4; ++x) {
-                tf += s_red[x];
-                tm = s_redm[x] > tm ? s_redm[x] : tm;
+            for (int x = 0; x < CLASS_NT / SPG_WAVE; ++x) {
+                tf += s_f[x];
+                tm = s_mb[x] > tm ? s_mb[x] : tm;
             }
-            finish_row(i, beg, end, tf, tm, bp, o, s_hist, s_flops, s_annz, &s_fmax);
+            finish(i, lb, le, tf, tm);
         }
         __syncthreads();
     }
-    flush_stats(o, s_hist, s_flops, s_annz, &s_fmax);
+    fmax = wave_reduce_max(fmax);
+    if (lane == 0 && fmax) atomicMax(&c.fmax, fmax);
+    c.flush(o.order, o.bin_stats, o.max_flops);
 }
 
-// Numeric classification from exact counts (after the symbolic scan).
-// A bitmap row keeps its rank paths only if the symbolic pass saved its
-// bitmap (heavy_idx >= 0; NULL = no bitmaps saved).
-__global__ void __launch_bounds__(256) k_num_classify(int64_t m, const int64_t* c_rp,
-                                                      const int64_t* a_beg, const int64_t* a_end,
-                                                      const int64_t* flops, BinParams bp,
-                                                      const int32_t* heavy_idx, uint8_t* bin, int64_t* bin_stats) {
-    __shared__ int s_hist[NBINS];
-    __shared__ int64_t s_flops[NBINS], s_annz[NBINS], s_cnnz[NBINS];
-    if (threadIdx.x < NBINS) {
-        s_hist[threadIdx.x] = 0;
-        s_flops[threadIdx.x] = 0;
-        s_annz[threadIdx.x] = 0;
-        s_cnnz[threadIdx.x] = 0;
-    }
-    __syncthreads();
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < m) {
-        int64_t cnt = c_rp[i + 1] - c_rp[i];
-        int64_t an = a_end[i] - a_beg[i];
-        int64_t f = flops[i];
-        const bool saved = bin[i] == BIN_DENSE && heavy_idx && heavy_idx[i] >= 0;
-        int b = num_bin(f, an, cnt, saved, bp);
-        bin[i] = (uint8_t)b;
-        atomicAdd(&s_hist[b], 1);
-        atomicAdd((unsigned long long*)&s_flops[b], (unsigned long long)f);
-        atomicAdd((unsigned long long*)&s_annz[b], (unsigned long long)an);
-        atomicAdd((unsigned long long*)&s_cnnz[b], (unsigned long long)cnt);
-    }
-    __syncthreads();
-    if (threadIdx.x < NBINS) {
-        int b = threadIdx.x;
-        if (s_hist[b]) {
-            atomicAdd((unsigned long long*)&bin_stats[b], (unsigned long long)s_hist[b]);
-            atomicAdd((unsigned long long*)&bin_stats[NBINS + b], (unsigned long long)s_flops[b]);
-            atomicAdd((unsigned long long*)&bin_stats[2 * NBINS + b], (unsigned long long)s_annz[b]);
-            atomicAdd((unsigned long long*)&bin_stats[3 * NBINS + b], (unsigned long long)s_cnnz[b]);
+// Numeric classification from exact counts, and the sums of the counts per
+// tile of CLASS_NT rows for the scan that follows (k_scan_scatter).  cnt[i] =
+// outputs of row i.  A bitmap row keeps its rank paths only if the symbolic
+// pass saved its bitmap (heavy_idx >= 0; NULL = no bitmaps saved).
+__global__ void __launch_bounds__(CLASS_NT) k_num_classify(int64_t m, const int64_t* cnt, const int64_t* a_beg,
+                                                           const int64_t* a_end, const int64_t* flops, BinParams bp,
+                                                           const int32_t* heavy_idx, uint8_t* bin, int64_t* bin_stats,
+                                                           OrderedBins order, int64_t* tile_sums) {
+    __shared__ ClassLds<3> c;
+    __shared__ int64_t red[CLASS_NT / SPG_WAVE + 1];
+    c.clear(order);
+    for (int64_t t0 = (int64_t)blockIdx.x * CLASS_NT; t0 < m; t0 += (int64_t)gridDim.x * CLASS_NT) {
+        const int64_t i = t0 + threadIdx.x;
+        int64_t n = 0;
+        if (i < m) {
+            n = cnt[i];
+            const int64_t an = a_end[i] - a_beg[i];
+            const int64_t f = flops[i];
+            const bool saved = bin[i] == BIN_DENSE && heavy_idx && heavy_idx[i] >= 0;
+            const int b = num_bin(f, an, n, saved, bp);
+            bin[i] = (uint8_t)b;
+            atomicAdd(&c.rows[b], 1);
+            atomicAdd(&c.v[0][b], (unsigned long long)f);
+            atomicAdd(&c.v[1][b], (unsigned long long)an);
+            atomicAdd(&c.v[2][b], (unsigned long long)n);
+            if (order.has(b)) atomicAdd(&c.lpt[order.key(b, f)], 1);
         }
+        int64_t total;
+        (void)block_exclusive_scan<CLASS_NT, int64_t>(n, &total, red);
+        if (threadIdx.x == 0) tile_sums[t0 / CLASS_NT] = total;
     }
+    c.flush(order, bin_stats, nullptr);
 }
 
-// Counting-sort scatter of rows into per-bin lists.  bin_stats[0..NBINS)
-// holds the per-bin row counts; list segment of bin b starts at the sum of
-// the counts of bins < b.  cursor[NBINS] must be zero on entry.
-__global__ void __launch_bounds__(256) k_bin_scatter(int64_t m, const uint8_t* bin,
-                                                     const int64_t* bin_counts, int32_t* cursor,
-                                                     int32_t* lists) {
-    __shared__ int s_cnt[NBINS];
-    __shared__ int s_base[NBINS];
-    if (threadIdx.x < NBINS) s_cnt[threadIdx.x] = 0;
-    __syncthreads();
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int b = -1, local = 0;
-    if (i < m) {
-        b = bin[i];
-        local = atomicAdd(&s_cnt[b], 1);
-    }
-    __syncthreads();
+// Counting-sort scatter of a tile's rows (one per thread, b < 0: none) into
+// per-bin lists: the list of bin b starts at the sum of the counts of the bins
+// below it (counts[0..NBINS)); a run of ordered bins is placed by its keys.
+// cursor[NBINS + order.keys()] must be zero before the first tile.
+struct ScatterLds {
+    int32_t cnt[NBINS + LPT_KEYS * LPT_MAX_BINS];
+    int32_t base[NBINS + LPT_KEYS * LPT_MAX_BINS];
+    int32_t red[CLASS_NT / SPG_WAVE + 1];
+};
+__device__ inline void scatter_tile(int64_t i, int b, const int64_t* counts, const OrderedBins& order, int32_t* cursor,
+                                    int32_t* lists, ScatterLds& S) {
+    const int nk = order.keys();
+    for (int k = threadIdx.x; k < NBINS + nk; k += CLASS_NT) S.cnt[k] = 0;
     if (threadIdx.x < NBINS) {
-        int bb = threadIdx.x;
         int64_t off = 0;
-        for (int x = 0; x < bb; ++x) off += bin_counts[x];
-        s_base[bb] = s_cnt[bb] ? (int)off + atomicAdd(&cursor[bb], s_cnt[bb]) : 0;
+        for (int x = 0; x < (int)threadIdx.x; ++x) off += counts[x];
+        S.base[threadIdx.x] = (int32_t)off;
     }
     __syncthreads();
-    if (b >= 0) lists[s_base[b] + local] = (int32_t)i;
-}
-
-// Longest-processing-time order of the row lists of a run of consecutive
-// bins [b_lo, b_lo + nb): within each bin, rows with more products first,
-// so that the heaviest workgroups start early and the end of a launch is not
-// held up by a large row that started last.  The bins' lists are contiguous,
-// so one counting sort over the run with key (bin - b_lo, work class) keeps
-// every bin in place; 256 work classes per bin, 8 per power of two of the
-// products (rows within about 12% of each other share a class).
-constexpr int LPT_KEYS = 256;
-constexpr int LPT_MAX_BINS = 8;
-__device__ inline int lpt_class(int64_t w) {
-    if (w < 1) w = 1;
-    const int e = 63 - __clzll((unsigned long long)w);  // floor(log2 w)
-    const int frac = e >= 3 ? (int)((w >> (e - 3)) & 7) : (int)((w << (3 - e)) & 7);
-    const int k = e * 8 + frac;
-    return LPT_KEYS - 1 - (k < LPT_KEYS - 1 ? k : LPT_KEYS - 1);  // more work: smaller class
-}
-__device__ inline int lpt_key(int32_t row, const uint8_t* bin, int b_lo, const int64_t* work) {
-    return ((int)bin[row] - b_lo) * LPT_KEYS + lpt_class(work[row]);
-}
-
-// The rows of bins [b_lo, b_hi) in the lists: offset and count from the
-// per-bin counts on the device.
-__device__ inline void bin_run(const int64_t* counts, int b_lo, int b_hi, int64_t& off, int64_t& n) {
-    off = 0;
-    for (int x = 0; x < b_lo; ++x) off += counts[x];
-    n = 0;
-    for (int x = b_lo; x < b_hi; ++x) n += counts[x];
-}
-
-__global__ void __launch_bounds__(256) k_lpt_hist(const int32_t* lists, const int64_t* counts, int b_lo, int b_hi,
-                                                  const uint8_t* bin, int nk, const int64_t* work, int32_t* hist) {
-    __shared__ int32_t s_h[LPT_KEYS * LPT_MAX_BINS];
-    int64_t off, n;
-    bin_run(counts, b_lo, b_hi, off, n);
-    if ((int64_t)blockIdx.x * 256 >= n) return;
-    for (int k = threadIdx.x; k < nk; k += 256) s_h[k] = 0;
-    __syncthreads();
-    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256)
-        atomicAdd(&s_h[lpt_key(lists[off + r], bin, b_lo, work)], 1);
-    __syncthreads();
-    for (int k = threadIdx.x; k < nk; k += 256)
-        if (s_h[k]) atomicAdd(&hist[k], s_h[k]);
-}
-
-// one workgroup: counts -> exclusive offsets, in place (nk <= 256 * LPT_MAX_BINS;
-// thread t owns keys [t * per, (t + 1) * per))
-__global__ void __launch_bounds__(256) k_lpt_scan(int32_t* hist, int nk) {
-    __shared__ int32_t tmp[256 / SPG_WAVE + 1];
-    const int per = (nk + 255) / 256;
-    const int k0 = threadIdx.x * per;
-    int32_t part = 0;
-    for (int k = k0; k < k0 + per && k < nk; ++k) part += hist[k];
-    int32_t total;
-    int32_t run = block_exclusive_scan<256, int32_t>(part, &total, tmp);
-    for (int k = k0; k < k0 + per && k < nk; ++k) {
-        const int32_t v = hist[k];
-        hist[k] = run;
-        run += v;
-    }
-}
-
-// Scatter by key; each 256-row tile of a workgroup takes its key bases with
-// one atomic per key.  tmp receives the ordered rows (n entries).
-__global__ void __launch_bounds__(256) k_lpt_scatter(const int32_t* lists, const int64_t* counts, int b_lo, int b_hi,
-                                                     const uint8_t* bin, int nk, const int64_t* work, int32_t* cursor,
-                                                     int32_t* tmp) {
-    __shared__ int32_t s_cnt[LPT_KEYS * LPT_MAX_BINS];
-    int64_t off, n;
-    bin_run(counts, b_lo, b_hi, off, n);
-    for (int64_t t0 = (int64_t)blockIdx.x * 256; t0 < n; t0 += (int64_t)gridDim.x * 256) {
-        for (int k = threadIdx.x; k < nk; k += 256) s_cnt[k] = 0;
-        __syncthreads();
-        const int64_t r = t0 + threadIdx.x;
-        int key = 0, local = 0, row = 0;
-        if (r < n) {
-            row = lists[off + r];
-            key = lpt_key(row, bin, b_lo, work);
-            local = atomicAdd(&s_cnt[key], 1);
+    if (nk > 0) {  // starts of the keys: a scan of their counts from the run's first bin
+        constexpr int PER = (LPT_KEYS * LPT_MAX_BINS + CLASS_NT - 1) / CLASS_NT;
+        int32_t h[PER], part = 0;
+#pragma unroll
+        for (int x = 0; x < PER; ++x) {
+            const int k = threadIdx.x * PER + x;
+            h[x] = k < nk ? order.hist[k] : 0;
+            part += h[x];
         }
-        __syncthreads();
-        for (int k = threadIdx.x; k < nk; k += 256)
-            if (s_cnt[k]) s_cnt[k] = atomicAdd(&cursor[k], s_cnt[k]);  // now the tile's base for key k
-        __syncthreads();
-        if (r < n) tmp[s_cnt[key] + local] = row;
-        __syncthreads();
+        int32_t total;
+        int32_t run = block_exclusive_scan<CLASS_NT, int32_t>(part, &total, S.red) + S.base[order.b_lo];
+#pragma unroll
+        for (int x = 0; x < PER; ++x) {
+            const int k = threadIdx.x * PER + x;
+            if (k < nk) S.base[NBINS + k] = run;
+            run += h[x];
+        }
     }
+    int key = 0, local = 0;
+    if (b >= 0) {
+        key = order.has(b) ? NBINS + order.key(b, order.work[i]) : b;
+        local = atomicAdd(&S.cnt[key], 1);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < NBINS + nk; k += CLASS_NT)
+        if (S.cnt[k]) S.base[k] += atomicAdd(&cursor[k], S.cnt[k]);
+    __syncthreads();
+    if (b >= 0) lists[S.base[key] + local] = (int32_t)i;
 }
 
-// The ordered rows back into the lists.
-__global__ void __launch_bounds__(256) k_lpt_copy(int32_t* lists, const int64_t* counts, int b_lo, int b_hi,
-                                                  const int32_t* tmp) {
-    int64_t off, n;
-    bin_run(counts, b_lo, b_hi, off, n);
-    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256)
-        lists[off + r] = tmp[r];
+// host (optional, pinned): receives words of the statistics
+__global__ void __launch_bounds__(CLASS_NT) k_bin_scatter(int64_t m, const uint8_t* bin, const int64_t* counts,
+                                                          OrderedBins order, int32_t* cursor, int32_t* lists,
+                                                          const int64_t* stats, int32_t words, int64_t* host) {
+    __shared__ ScatterLds S;
+    if (host && blockIdx.x == 0)
+        for (int t = threadIdx.x; t < words; t += CLASS_NT)
+            __hip_atomic_store(&host[t], stats[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const int64_t i = (int64_t)blockIdx.x * CLASS_NT + threadIdx.x;
+    scatter_tile(i, i < m ? (int)bin[i] : -1, counts, order, cursor, lists, S);
+}
+
+// Row pointers and bin lists after k_num_classify, one tile per workgroup:
+// rp[0] = 0, rp[i + 1] = inclusive sum of the counts, in place (rp[i + 1] holds
+// row i's count; each workgroup sums the tiles before its own itself), and
+// the tile's rows into the lists.  host (optional, pinned): receives words of
+// the statistics, then nnz(C).
+__global__ void __launch_bounds__(CLASS_NT) k_scan_scatter(int64_t m, int64_t* rp, const int64_t* tile_sums,
+                                                           const uint8_t* bin, const int64_t* counts, OrderedBins order,
+                                                           int32_t* cursor, int32_t* lists, const int64_t* stats,
+                                                           int32_t words, int64_t* host) {
+    __shared__ ScatterLds S;
+    __shared__ int64_t red[CLASS_NT / SPG_WAVE + 1];
+    const int64_t i = (int64_t)blockIdx.x * CLASS_NT + threadIdx.x;
+    int64_t before = 0;
+    for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += CLASS_NT) before += tile_sums[t];
+    const int64_t n = i < m ? rp[i + 1] : 0;
+    int64_t base, total;
+    (void)block_exclusive_scan<CLASS_NT, int64_t>(before, &base, red);
+    const int64_t pre = block_exclusive_scan<CLASS_NT, int64_t>(n, &total, red);
+    if (i < m) rp[i + 1] = base + pre + n;
+    if (i == 0) rp[0] = 0;
+    if (host) {
+        if (blockIdx.x == 0)
+            for (int t = threadIdx.x; t < words; t += CLASS_NT)
+                __hip_atomic_store(&host[t], stats[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (i == m - 1) __hip_atomic_store(&host[words], base + pre + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    scatter_tile(i, i < m ? (int)bin[i] : -1, counts, order, cursor, lists, S);
 }
 
 }  // namespace spg

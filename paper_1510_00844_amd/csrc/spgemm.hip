@@ -119,11 +119,11 @@ struct spg_plan_s {
     int num_cu = 256;
 
     // per-row state of the current product
-    DevBuf a_beg, a_end, flops, maxb, bin, lists, long_rows, small_i32, stats, tiles, split;
+    DevBuf a_beg, a_end, flops, maxb, bin, lists, small_i32, stats, tiles, split;
     DevBuf merge_len, mbin, mlists, mstats, mctr, bm_save, heavy_idx, chunk_save, rank_items;
-    DevBuf lpt_hist, lpt_tmp;  // ordering of heavy bins by work
     const int64_t* out_pos = nullptr;  // numeric output offsets per row (set while a sub-product writes into a full one)
-    int64_t* h_stats = nullptr;  // pinned, STATS_WORDS + 8 (nnz of the last read-back at STATS_WORDS)
+    int64_t* h_stats = nullptr;      // pinned, STATS_WORDS + 8 (nnz of the last read-back at STATS_WORDS)
+    int64_t* h_stats_dev = nullptr;  // its device address: kernels write the counts there themselves
 
     Signature sig;
     int64_t sig_rows = 0;       // rows of the current symbolic call (bounds launch grids)
@@ -218,18 +218,38 @@ static spg_status launch(spg_plan P, const std::string& name, F&& f) {
 // Fork: helper streams wait for everything queued so far on the caller's
 // stream.  Join: the caller's stream waits for the helpers.  Between the two,
 // independent bins are spread over the streams so their kernels overlap.
-static spg_status fork_streams(spg_plan P) {
+static spg_status fork_streams(spg_plan P, int naux) {
+    if (naux == 0) return SPG_OK;
     HIP_TRY(hipEventRecord(P->ev_fork, P->stream));
-    for (int k = 0; k < NAUX; ++k) HIP_TRY(hipStreamWaitEvent(P->aux[k], P->ev_fork, 0));
+    for (int k = 0; k < naux; ++k) HIP_TRY(hipStreamWaitEvent(P->aux[k], P->ev_fork, 0));
     return SPG_OK;
 }
-static spg_status join_streams(spg_plan P) {
-    for (int k = 0; k < NAUX; ++k) {
+static spg_status join_streams(spg_plan P, int naux) {
+    for (int k = 0; k < naux; ++k) {
         HIP_TRY(hipEventRecord(P->ev_join[k], P->aux[k]));
         HIP_TRY(hipStreamWaitEvent(P->stream, P->ev_join[k], 0));
     }
     P->cur = nullptr;
     return SPG_OK;
+}
+// Whether a phase's bins are spread over the helper streams at all.  A fork
+// and a join cost ten calls on the host and waits between the GPU's queues,
+// about 50 us a phase measured; what they save is the ramp and the tail of
+// each kernel that does not fill the GPU.  So: from six bins with rows on
+// (power-law matrices; uniform ones and stencils have fewer, and their one or
+// two large bins fill the GPU by themselves), and not for few products.
+// One stream against four: 65,536 products 72 / 179 us; ER scale 18 (5 bins)
+// 1170 / 1203; R-MAT scale 16 (12 bins) 1926 / 1729.
+static const int64_t FORK_MIN_PRODUCTS = 1 << 20;
+static const int FORK_MIN_BINS = 6;
+static bool worth_forking(const int64_t* counts) {
+    int64_t products = 0;
+    int bins = 0;
+    for (int b = 1; b < NBINS; ++b) {
+        products += counts[NBINS + b];
+        bins += counts[b] > 0;
+    }
+    return products >= FORK_MIN_PRODUCTS && bins >= FORK_MIN_BINS;
 }
 // Bins go to streams longest-processing-time first: each bin (in order of
 // decreasing work) to the stream with the least work so far; the first
@@ -254,6 +274,7 @@ struct StreamLoad {
         int nonempty = 0;
         for (int b = 1; b < NBINS; ++b) nonempty += counts[b] > 0;
         nstreams = std::max(1, std::min(P->opts.streams, std::max(heavy, nonempty > 1 ? 2 : 1)));
+        if (!worth_forking(counts)) nstreams = 1;
     }
 };
 static void use_stream(spg_plan P, StreamLoad& L, int pos, const int64_t* counts, int bin) {
@@ -278,30 +299,33 @@ static std::vector<int> bins_by_work(const int64_t* rows, const int64_t* work) {
 
 static inline unsigned grid_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-// The row analysis strides 16 rows per workgroup step; each workgroup adds
-// its per-bin statistics to a few global counters once, and device-wide
-// atomics on one address serialize across the XCDs, so the grid is kept to
-// 1024 workgroups.
-static inline unsigned rowinfo_grid(int64_t m) { return (unsigned)std::min<int64_t>(grid_for(m, 16), 1024); }
+// Row analysis: 64 rows per workgroup step, few workgroups (each adds its
+// statistics to the global counters once).
+static inline unsigned rowinfo_grid(int64_t m) { return (unsigned)std::min<int64_t>(grid_for(m, CLASS_NT / 16), 512); }
+// Numeric classification: a tile of CLASS_NT rows per workgroup step.
+static inline unsigned classify_grid(int64_t m) { return (unsigned)std::min<int64_t>(grid_for(m, CLASS_NT), 128); }
 
 // static LDS of k_num_rank<*, 512> (A values, product offsets, scan scratch), with margin
 static const int RANK_STATIC_LDS = (int)(8 * 512 + sizeof(ProductLds<512>) + 4 * 16 + 256);
 static const int RANK_STATIC_LDS_1024 = (int)(8 * 1024 + sizeof(ProductLds<1024>) + 4 * 32 + 256);
 static int rank_static_lds(spg_plan P) { return P->opts.rank_block == 1024 ? RANK_STATIC_LDS_1024 : RANK_STATIC_LDS; }
 // small counters and flags (int32), one size, never reallocated:
-//   [0]         long-row queue length (row analysis)
-//   [1, 17)     bin cursors of the symbolic classification
-//   [33, 49)    bin cursors of the numeric classification
-//   [96]        the CSR check flag
-//   [100]       the rank-chunk item count
-static const int SMALL_WORDS = 128;
-static const int CTR_SYM_CURSOR = 1, CTR_NUM_CURSOR = 33, CTR_CHECK = 96, CTR_RANK_ITEMS = 100;
+//   [0, 8)      the CSR check flag, the learned mode's and the stages' counters
+//   [8]         the rank-chunk item count
+//   then        the cursors (bins and work classes) and the work-class counts
+//               of the symbolic and of the numeric classification
+static const int SYM_LPT = LPT_KEYS, NUM_LPT = LPT_KEYS * LPT_MAX_BINS;  // work classes of the ordered bins
+static const int CTR_CHECK = 0, CTR_RANK_ITEMS = 8, CTR_SYM_CURSOR = 16;
+static const int CTR_SYM_HIST = CTR_SYM_CURSOR + NBINS + SYM_LPT, CTR_NUM_CURSOR = CTR_SYM_HIST + SYM_LPT;
+static const int CTR_NUM_HIST = CTR_NUM_CURSOR + NBINS + NUM_LPT, SMALL_WORDS = CTR_NUM_HIST + NUM_LPT;
 // per-bin statistics (int64): [0, 4 NBINS) the numeric classification (rows,
 // flops, A entries, outputs), [4 NBINS] the largest row's products,
 // [STATS_SYM, STATS_SYM + 3 NBINS) the symbolic classification (rows, flops,
 // A entries)
 static const int STATS_SYM = 4 * NBINS + 8;
 static const int STATS_WORDS = STATS_SYM + 3 * NBINS;
+static_assert(BIN_RANK0 + 3 - BIN_DENSE_PAR == LPT_MAX_BINS, "the heavy numeric bins are the ordered ones");
+static_assert(STATS_WORDS <= SMALL_WORDS, "one launch clears both");
 
 // ---------------------------------------------------------------------------
 // public helpers
@@ -534,6 +558,12 @@ extern "C" spg_status spg_plan_create(spg_plan* out, void* stream, const spg_opt
         hipGetLastError();
         return fail(SPG_ERR_OOM, "pinned host allocation failed");
     }
+    if (hipHostGetDevicePointer((void**)&P->h_stats_dev, P->h_stats, 0) != hipSuccess) {
+        hipHostFree(P->h_stats);
+        delete P;
+        hipGetLastError();
+        return fail(SPG_ERR_HIP, "pinned host memory has no device address");
+    }
     // LDS beyond 64 KiB for the kernels sized at launch
     set_lds_attributes<0>(P);
     set_lds_attributes<1>(P);
@@ -551,10 +581,9 @@ extern "C" spg_status spg_plan_destroy(spg_plan P) {
     if (!P) return SPG_OK;
     hipStreamSynchronize(P->stream);
     spg_release_galerkin(P);
-    for (DevBuf* b : {&P->a_beg, &P->a_end, &P->flops, &P->maxb, &P->bin, &P->lists, &P->long_rows,
+    for (DevBuf* b : {&P->a_beg, &P->a_end, &P->flops, &P->maxb, &P->bin, &P->lists,
                       &P->small_i32, &P->stats, &P->tiles, &P->split, &P->merge_len,
                       &P->mbin, &P->mlists, &P->mstats, &P->mctr, &P->bm_save, &P->heavy_idx, &P->chunk_save, &P->rank_items,
-                      &P->lpt_hist, &P->lpt_tmp,
                       &P->lcap, &P->lcnt, &P->slot, &P->pcol, &P->pval, &P->fb_list, &P->fb_redo, &P->sub_rp,
                       &P->sub_col, &P->sub_val, &P->sub_crp, &P->mlp_tmp, &P->sub_pos,
                       &P->mis_m1, &P->mis_cand, &P->mis_new, &P->mis_a1, &P->mis_flags, &P->mis_agg1,
@@ -649,6 +678,13 @@ __global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
     if (i < n) p[i] = v;
 }
 
+// both counter arrays to zero in one launch
+__global__ void k_clear_counters(int64_t* a, int32_t na, int32_t* b, int32_t nb) {
+    const int32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < na) a[i] = 0;
+    if (i < nb) b[i] = 0;
+}
+
 static spg_status fill_i32(spg_plan P, int32_t* p, int64_t n, int32_t v) {
     if (n <= 0) return SPG_OK;
     return launch(P, "fill", [&] { k_fill_i32<<<grid_for(n, 256), 256, 0, cs(P)>>>(p, n, v); });
@@ -657,33 +693,6 @@ static spg_status fill_i64(spg_plan P, int64_t* p, int64_t n, int64_t v) {
     if (n <= 0) return SPG_OK;
     return launch(P, "fill", [&] { k_fill_i64<<<grid_for(n, 256), 256, 0, cs(P)>>>(p, n, v); });
 }
-
-// Orders the row lists of bins [b_lo, b_hi) (contiguous in P->lists) by
-// decreasing products within each bin (counting sort, four kernels), with
-// the bins located from the per-bin counts on the device: no host copy of
-// the counts is needed, and no launch depends on them.
-static_assert(NBINS - BIN_DENSE_PAR <= LPT_MAX_BINS, "the heavy numeric bins fit one work ordering");
-static spg_status order_by_work(spg_plan P, int b_lo, int b_hi, const int64_t* counts, int64_t max_rows) {
-    if (max_rows < 2) return SPG_OK;
-    const int nk = (b_hi - b_lo) * LPT_KEYS;
-    int32_t* lists = P->lists.as<int32_t>();
-    int32_t* hist = P->lpt_hist.as<int32_t>();
-    int32_t* tmp = P->lpt_tmp.as<int32_t>();
-    const int64_t* work = P->flops.as<int64_t>();
-    const uint8_t* bin = P->bin.as<uint8_t>();
-    const unsigned grid = (unsigned)std::min<int64_t>(grid_for(max_rows, 256), 1024);
-    SPG_TRY(fill_i32(P, hist, nk, 0));
-    SPG_TRY(launch(P, "work_order", [&] {
-        k_lpt_hist<<<grid, 256, 0, cs(P)>>>(lists, counts, b_lo, b_hi, bin, nk, work, hist);
-    }));
-    SPG_TRY(launch(P, "work_order", [&] { k_lpt_scan<<<1, 256, 0, cs(P)>>>(hist, nk); }));
-    SPG_TRY(launch(P, "work_order", [&] {
-        k_lpt_scatter<<<grid, 256, 0, cs(P)>>>(lists, counts, b_lo, b_hi, bin, nk, work, hist, tmp);
-    }));
-    SPG_TRY(launch(P, "work_order", [&] { k_lpt_copy<<<grid, 256, 0, cs(P)>>>(lists, counts, b_lo, b_hi, tmp); }));
-    return SPG_OK;
-}
-
 
 static spg_status validate_csr(spg_plan P, const spg_csr* M, const char* name) {
     if (M->nrows == 0) return SPG_OK;
@@ -704,17 +713,18 @@ static spg_status validate_csr(spg_plan P, const spg_csr* M, const char* name) {
 // ---------------------------------------------------------------------------
 // tiles: (m / SCAN_TILE + 2) int64 of scratch (NULL: the plan's)
 static spg_status scan_counts(spg_plan P, int64_t* rp, int64_t m, int64_t* tiles = nullptr) {
-    SPG_TRY(fill_i64(P, rp, 1, 0));
-    if (m == 0) return SPG_OK;
+    if (m == 0) return fill_i64(P, rp, 1, 0);
     const int64_t ntiles = (m + SCAN_TILE - 1) / SCAN_TILE;
     if (!tiles) {
         SPG_TRY(P->tiles.ensure(sizeof(int64_t) * (ntiles + 1), "scan tiles"));
         tiles = P->tiles.as<int64_t>();
     }
-    int64_t* cnt = rp + 1;
-    SPG_TRY(launch(P, "scan", [&] { k_scan_tiles<<<(unsigned)ntiles, SCAN_NT, 0, cs(P)>>>(cnt, m, tiles); }));
-    SPG_TRY(launch(P, "scan", [&] { k_scan_top<<<1, SCAN_NT, 0, cs(P)>>>(tiles, ntiles); }));
-    SPG_TRY(launch(P, "scan", [&] { k_scan_apply<<<(unsigned)ntiles, SCAN_NT, 0, cs(P)>>>(cnt, m, tiles, cnt); }));
+    const bool top = ntiles > SCAN_SELF;
+    SPG_TRY(launch(P, "scan", [&] { k_scan_tiles<<<(unsigned)ntiles, SCAN_NT, 0, cs(P)>>>(rp + 1, m, tiles); }));
+    if (top) SPG_TRY(launch(P, "scan", [&] { k_scan_top<<<1, SCAN_NT, 0, cs(P)>>>(tiles, ntiles); }));
+    SPG_TRY(launch(P, "scan", [&] {
+        k_scan_apply<<<(unsigned)ntiles, SCAN_NT, 0, cs(P)>>>(rp, m, tiles, top ? 1 : 0);
+    }));
     return SPG_OK;
 }
 
@@ -726,9 +736,6 @@ static spg_status ensure_rows(spg_plan P, int64_t m) {
     SPG_TRY(P->maxb.ensure(4 * mm, "maxb"));
     SPG_TRY(P->bin.ensure(mm, "bin"));
     SPG_TRY(P->lists.ensure(4 * mm, "bin lists"));
-    SPG_TRY(P->lpt_tmp.ensure(4 * mm, "work order"));
-    SPG_TRY(P->lpt_hist.ensure(sizeof(int32_t) * LPT_MAX_BINS * LPT_KEYS, "work order"));
-    SPG_TRY(P->long_rows.ensure(4 * mm, "long rows"));
     SPG_TRY(P->small_i32.ensure(SMALL_WORDS * 4, "counters"));
     SPG_TRY(P->stats.ensure(sizeof(int64_t) * STATS_WORDS, "bin stats"));
     return SPG_OK;
@@ -872,13 +879,16 @@ static spg_status host_wait(spg_plan P) {
 }
 
 // Reads back (synchronizing) the classification counts of the last
-// symbolic call and nnz(C); the bitmap bin's count sizes the saved bitmaps
-// of the next call with the same operands.
-static spg_status read_counts(spg_plan P, const int64_t* c_row_ptr, int64_t m) {
-    const int64_t* stats = P->stats.as<int64_t>();
-    HIP_TRY(hipMemcpyAsync(P->h_stats, stats, sizeof(int64_t) * STATS_WORDS, hipMemcpyDeviceToHost, P->stream));
-    HIP_TRY(hipMemcpyAsync(P->h_stats + STATS_WORDS, c_row_ptr + m, sizeof(int64_t), hipMemcpyDeviceToHost,
-                           P->stream));
+// symbolic call and nnz(C) (on_host: its last kernel has written them to the
+// pinned buffer already); the bitmap bin's count sizes the saved bitmaps of
+// the next call with the same operands.
+static spg_status read_counts(spg_plan P, const int64_t* c_row_ptr, int64_t m, bool on_host) {
+    if (!on_host) {
+        const int64_t* stats = P->stats.as<int64_t>();
+        HIP_TRY(hipMemcpyAsync(P->h_stats, stats, sizeof(int64_t) * STATS_WORDS, hipMemcpyDeviceToHost, P->stream));
+        HIP_TRY(hipMemcpyAsync(P->h_stats + STATS_WORDS, c_row_ptr + m, sizeof(int64_t), hipMemcpyDeviceToHost,
+                               P->stream));
+    }
     SPG_TRY(host_wait(P));
     const int64_t nnz = P->h_stats[STATS_WORDS];
     std::memcpy(P->num_counts, P->h_stats, sizeof(int64_t) * 4 * NBINS);
@@ -944,23 +954,11 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
     int32_t* lists = P->lists.as<int32_t>();
     const int32_t W = P->opts.dense_chunk_cols;
 
-    SPG_TRY(fill_i64(P, stats, STATS_WORDS, 0));
-    SPG_TRY(fill_i32(P, ctr, SMALL_WORDS, 0));
+    // the bins whose rows are ordered by work, of each classification
+    const OrderedBins sorder{BIN_DENSE, BIN_DENSE + 1, ctr + CTR_SYM_HIST, P->flops.as<int64_t>()};
+    const OrderedBins norder{BIN_DENSE_PAR, BIN_RANK0 + 3, ctr + CTR_NUM_HIST, P->flops.as<int64_t>()};
     RowInfoOut o{P->a_beg.as<int64_t>(), P->a_end.as<int64_t>(), P->flops.as<int64_t>(), P->maxb.as<int32_t>(),
-                 P->bin.as<uint8_t>(), cnt, sstats, P->long_rows.as<int32_t>(), ctr,
-                 (unsigned long long*)(stats + 4 * NBINS)};
-    if (m > 0) {
-        SPG_TRY(launch(P, "rowinfo", [&] {
-            k_rowinfo<<<rowinfo_grid(m), 256, 0, cs(P)>>>(a, b, k_lo, k_hi, full, bp, o);
-        }));
-        SPG_TRY(launch(P, "rowinfo_long", [&] {
-            k_rowinfo_long<<<256, 256, 0, cs(P)>>>(a, b, k_lo, k_hi, full, bp, o);
-        }));
-        SPG_TRY(launch(P, "bin_scatter", [&] {
-            k_bin_scatter<<<grid_for(m, 256), 256, 0, cs(P)>>>(m, P->bin.as<uint8_t>(), sstats, ctr + CTR_SYM_CURSOR,
-                                                                   lists);
-        }));
-    }
+                 P->bin.as<uint8_t>(), cnt, sstats, (unsigned long long*)(stats + 4 * NBINS), sorder};
     Signature sg;
     sg.a_rp = A->row_ptr; sg.a_col = A->col; sg.b_rp = B->row_ptr; sg.b_col = B->col;
     sg.m = m; sg.n = n; sg.k = A->ncols; sg.annz = A->nnz; sg.bnnz = B->nnz; sg.k_lo = k_lo; sg.k_hi = k_hi;
@@ -970,7 +968,8 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
     // enumerators' int32 counts, so such a row is rejected before any bin
     // runs).  Later calls with the same operands use the last call's count
     // and queue everything without waiting.
-    // Bin row counts that size the grids: read back now the first time these
+    // Bin row counts that size the grids: read back now (the scatter kernel
+    // writes them to pinned host memory) the first time these
     // operands are seen (exact), else those of the last call with them
     // (checked against the real counts at the final readback).  A graph
     // capture (frozen) reuses the eager call's counts.
@@ -978,16 +977,29 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
     int64_t hint[2 * NBINS];
     bool exact = true;
     const bool known = P->bm_rows >= 0 && P->bm_sig == sg && bp.dense_ok && c_nnz != nullptr && !fresh;
-    if (P->frozen || known) {
+    const bool reuse = P->frozen || known;
+    if (m > 0) {
+        SPG_TRY(launch(P, "fill", [&] {
+            k_clear_counters<<<grid_for(SMALL_WORDS, 256), 256, 0, cs(P)>>>(stats, STATS_WORDS, ctr, SMALL_WORDS);
+        }));
+        SPG_TRY(launch(P, "rowinfo", [&] {
+            k_rowinfo<<<rowinfo_grid(m), CLASS_NT, 0, cs(P)>>>(a, b, k_lo, k_hi, full, bp, o);
+        }));
+        SPG_TRY(launch(P, "bin_scatter", [&] {
+            k_bin_scatter<<<grid_for(m, CLASS_NT), CLASS_NT, 0, cs(P)>>>(m, P->bin.as<uint8_t>(), sstats, sorder,
+                                                                         ctr + CTR_SYM_CURSOR, lists, stats, STATS_WORDS,
+                                                                         reuse ? nullptr : P->h_stats_dev);
+        }));
+    } else {
+        SPG_TRY(fill_i64(P, stats, STATS_WORDS, 0));
+    }
+    if (reuse) {
         std::memcpy(hint, P->sym_counts, sizeof(hint));
         exact = P->frozen;
     } else if (m > 0) {
-        HIP_TRY(hipMemcpyAsync(P->h_stats, sstats, sizeof(hint), hipMemcpyDeviceToHost, P->stream));
-        HIP_TRY(hipMemcpyAsync(P->h_stats + 2 * NBINS, stats + 4 * NBINS, sizeof(int64_t), hipMemcpyDeviceToHost,
-                               P->stream));
         SPG_TRY(host_wait(P));
-        SPG_TRY(check_row_products(bp, P->h_stats[2 * NBINS]));
-        std::memcpy(hint, P->h_stats, sizeof(hint));
+        SPG_TRY(check_row_products(bp, P->h_stats[4 * NBINS]));
+        std::memcpy(hint, P->h_stats + STATS_SYM, sizeof(hint));
     } else {
         std::memset(hint, 0, sizeof(hint));
     }
@@ -995,8 +1007,9 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
 
     // per-bin accumulators: the bitmap rows (heaviest first) on the plan's
     // stream, the other bins round robin over the helper streams
-    const int nstreams = std::max(1, std::min(P->opts.streams, NAUX + 1));
-    SPG_TRY(fork_streams(P));
+    int nstreams = std::max(1, std::min(P->opts.streams, NAUX + 1));
+    if (!worth_forking(hint)) nstreams = 1;
+    SPG_TRY(fork_streams(P, nstreams - 1));
     // the numeric pass's split table (B and W only) on the last helper stream
     // when rank-chunk items are possible (chunk counts recorded, bitmap rows
     // expected) and a row has more than one chunk; the numeric pass builds
@@ -1010,7 +1023,6 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
         P->split_ready = true;
     }
     P->cur = P->stream;
-    if (m > 0 && hint[BIN_DENSE] > 0) SPG_TRY(order_by_work(P, BIN_DENSE, BIN_DENSE + 1, sstats, hint[BIN_DENSE]));
     if (m > 0) {
         const int32_t nwords = (int32_t)std::min<int64_t>((n + 31) / 32, 1 << 14);
         uint32_t* save = nullptr;
@@ -1078,25 +1090,28 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
             }
         }
     }
-    SPG_TRY(join_streams(P));
-    SPG_TRY(scan_counts(P, c_row_ptr, m));
+    SPG_TRY(join_streams(P, nstreams - 1));
 
-    // numeric classification from the exact counts, and the numeric pass's
-    // preparation: heavy rows ordered by work, the rank-chunk items
-    if (m > 0) {
+    // numeric classification from the exact counts, the row pointers, and the
+    // numeric pass's preparation: row lists (heavy rows ordered by work) and
+    // the rank-chunk items; the counts and nnz(C) go to pinned host memory
+    const bool to_host = c_nnz != nullptr && !P->frozen;
+    if (m == 0) {
+        SPG_TRY(fill_i64(P, c_row_ptr, 1, 0));
+    } else {
+        SPG_TRY(P->tiles.ensure(sizeof(int64_t) * (size_t)grid_for(m, CLASS_NT), "scan tiles"));
+        int64_t* tiles = P->tiles.as<int64_t>();
         SPG_TRY(launch(P, "num_classify", [&] {
-            k_num_classify<<<grid_for(m, 256), 256, 0, cs(P)>>>(m, c_row_ptr, P->a_beg.as<int64_t>(),
-                                                                    P->a_end.as<int64_t>(), P->flops.as<int64_t>(),
-                                                                    bp, P->bm_cap > 0 ? P->heavy_idx.as<int32_t>() : nullptr,
-                                                                    P->bin.as<uint8_t>(), nstats);
+            k_num_classify<<<classify_grid(m), CLASS_NT, 0, cs(P)>>>(
+                m, cnt, P->a_beg.as<int64_t>(), P->a_end.as<int64_t>(), P->flops.as<int64_t>(), bp,
+                P->bm_cap > 0 ? P->heavy_idx.as<int32_t>() : nullptr, P->bin.as<uint8_t>(), nstats, norder, tiles);
         }));
-        SPG_TRY(launch(P, "bin_scatter", [&] {
-            k_bin_scatter<<<grid_for(m, 256), 256, 0, cs(P)>>>(m, P->bin.as<uint8_t>(), nstats, ctr + CTR_NUM_CURSOR,
-                                                                   lists);
+        SPG_TRY(launch(P, "scan", [&] {
+            k_scan_scatter<<<grid_for(m, CLASS_NT), CLASS_NT, 0, cs(P)>>>(
+                m, c_row_ptr, tiles, P->bin.as<uint8_t>(), nstats, norder, ctr + CTR_NUM_CURSOR, lists, stats,
+                STATS_WORDS, to_host ? P->h_stats_dev : nullptr);
         }));
-        // the heavy numeric bins are among the saved bitmap rows
         const int64_t slots_used = P->bm_cap;
-        if (slots_used > 0) SPG_TRY(order_by_work(P, BIN_DENSE_PAR, BIN_RANK0 + 3, nstats, slots_used));
         if (chunked && slots_used > 0) {
             const int32_t chunks = (int32_t)((b.ncols + W - 1) / W);
             SPG_TRY(P->rank_items.ensure(sizeof(RankItem) * (size_t)std::max<int64_t>(
@@ -1119,7 +1134,7 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
     }
     P->last_crp = c_row_ptr;
     if (c_nnz) {
-        SPG_TRY(read_counts(P, c_row_ptr, m));
+        SPG_TRY(read_counts(P, c_row_ptr, m, to_host && m > 0));
         // a bin skipped as empty by the last call's counts that now holds
         // rows: the structure behind the same pointers changed; redo with
         // counts read back first
@@ -1196,9 +1211,9 @@ static spg_status numeric_sr(spg_plan P, Csr a, Csr b, const int64_t* c_row_ptr,
         SPG_TRY(build_split_table(P, b, W));
         P->split_ready = true;
     }
-    SPG_TRY(fork_streams(P));
     const std::vector<int> num_order = bins_by_work(P->num_counts, P->num_counts + NBINS);
     StreamLoad nload(P, P->num_counts);
+    SPG_TRY(fork_streams(P, nload.nstreams - 1));
     for (size_t oi = 0; oi < num_order.size(); ++oi) {
         const int bb = num_order[oi];
         const int64_t nr = P->num_counts[bb];
@@ -1282,7 +1297,7 @@ static spg_status numeric_sr(spg_plan P, Csr a, Csr b, const int64_t* c_row_ptr,
             SPG_TRY(num_hash_dispatch<SR>(P, HASH_MIN_LOG2 + (bb - BIN_HASH0), a, b, rows, nr, crp, ccol, cval));
         }
     }
-    SPG_TRY(join_streams(P));
+    SPG_TRY(join_streams(P, nload.nstreams - 1));
     return SPG_OK;
 }
 
@@ -1301,7 +1316,7 @@ extern "C" spg_status spgemm_numeric(spg_plan P, spg_semiring sr, const spg_csr*
     s.m = A->nrows; s.n = B->ncols; s.k = A->ncols; s.annz = A->nnz; s.bnnz = B->nnz; s.k_lo = k_lo; s.k_hi = k_hi;
     if (!P->have_symbolic || !(s == P->sig))
         return fail(SPG_ERR_STATE, "spgemm_numeric needs the matching spgemm_symbolic on this plan first");
-    if (!P->num_counts_valid) SPG_TRY(read_counts(P, c_row_ptr, s.m));
+    if (!P->num_counts_valid) SPG_TRY(read_counts(P, c_row_ptr, s.m, false));
     if (P->last_nnz > 0 && !c_col) return fail(SPG_ERR_ARG, "c_col is NULL");
     Csr a = view(A), b = view(B);
     switch (sr) {
@@ -1426,7 +1441,8 @@ static spg_status merge_classify(spg_plan P, int32_t c, const LayerSet& ls, int6
                                                                                                  mstats);
         }));
         SPG_TRY(launch(P, "bin_scatter", [&] {
-            k_bin_scatter<<<grid_for(m, 256), 256, 0, cs(P)>>>(m, mbin, mstats, mctr, mlists);
+            k_bin_scatter<<<grid_for(m, CLASS_NT), CLASS_NT, 0, cs(P)>>>(
+                m, mbin, mstats, OrderedBins{0, 0, nullptr, nullptr}, mctr, mlists, mstats, 0, nullptr);
         }));
     }
     HIP_TRY(hipMemcpyAsync(host_buf, mstats, sizeof(int64_t) * MBINS, hipMemcpyDeviceToHost, P->stream));
@@ -1842,7 +1858,7 @@ extern "C" spg_status spgemm_summa_local(spg_plan P, spg_semiring sr, const spg_
 extern "C" spg_status spg_plan_stats(spg_plan P, spg_stats* out) {
     if (!P || !out) return fail(SPG_ERR_ARG, "NULL argument");
     if (P->have_symbolic && !P->num_counts_valid && !P->frozen && P->last_crp)
-        SPG_TRY(read_counts(P, P->last_crp, P->sig.m));
+        SPG_TRY(read_counts(P, P->last_crp, P->sig.m, false));
     std::memset(out, 0, sizeof(*out));
     out->m = P->sig.m;
     out->n = P->sig.n;
@@ -1995,12 +2011,9 @@ static spg_status learned_launch(spg_plan P, Csr a, Csr b, int32_t nwords) {
     int64_t bin_off[NBINS + 1];
     bin_off[0] = 0;
     for (int x = 0; x < NBINS; ++x) bin_off[x + 1] = bin_off[x] + P->l_counts[x];
-    // the fused bitmap-rank rows (bins 13..15), heaviest first
-    SPG_TRY(order_by_work(P, BIN_DENSE_PAR, BIN_RANK0 + 3, P->stats.as<int64_t>(),
-                          bin_off[BIN_RANK0 + 3] - bin_off[BIN_DENSE_PAR]));
-    SPG_TRY(fork_streams(P));
     const std::vector<int> order = bins_by_work(P->l_counts, P->l_counts + NBINS);
     StreamLoad lload(P, P->l_counts);
+    SPG_TRY(fork_streams(P, lload.nstreams - 1));
     for (size_t oi = 0; oi < order.size(); ++oi) {
         const int bb = order[oi];
         const int64_t nr = P->l_counts[bb];
@@ -2027,7 +2040,7 @@ static spg_status learned_launch(spg_plan P, Csr a, Csr b, int32_t nwords) {
             SPG_TRY(num_hash_dispatch<SR>(P, HASH_MIN_LOG2 + (bb - BIN_HASH0), a, b, rows, nr, slot, pcol, pval, cnt));
         }
     }
-    return join_streams(P);
+    return join_streams(P, lload.nstreams - 1);
 }
 
 template <int SR>
@@ -2099,11 +2112,14 @@ extern "C" spg_status spgemm_learned_run(spg_plan P, spg_semiring sr, const spg_
     int32_t* ctr = P->small_i32.as<int32_t>();
     int64_t* cnt = P->lcnt.as<int64_t>() + 1;
     const int full = (k_lo == 0 && k_hi == A->ncols) ? 1 : 0;
-    SPG_TRY(fill_i64(P, stats, 4 * NBINS + 1, 0));
-    SPG_TRY(fill_i32(P, ctr, 2 + NBINS, 0));
+    // row analysis statistics apart from the learned classification's
+    SPG_TRY(launch(P, "fill", [&] {
+        k_clear_counters<<<grid_for(SMALL_WORDS, 256), 256, 0, cs(P)>>>(stats, STATS_WORDS, ctr, SMALL_WORDS);
+    }));
+    const OrderedBins lorder{BIN_RANK0, BIN_RANK0 + 3, ctr + CTR_NUM_HIST, P->flops.as<int64_t>()};
     RowInfoOut o{P->a_beg.as<int64_t>(), P->a_end.as<int64_t>(), P->flops.as<int64_t>(), P->maxb.as<int32_t>(),
-                 P->bin.as<uint8_t>(), cnt, stats, P->long_rows.as<int32_t>(), ctr,
-                 (unsigned long long*)(stats + 4 * NBINS)};
+                 P->bin.as<uint8_t>(), cnt, stats + STATS_SYM, (unsigned long long*)(stats + 4 * NBINS),
+                 OrderedBins{0, 0, nullptr, nullptr}};
     LearnedParams lp;
     lp.margin = margin;
     lp.use_mlp = mlp_params ? 1 : 0;
@@ -2111,21 +2127,18 @@ extern "C" spg_status spgemm_learned_run(spg_plan P, spg_semiring sr, const spg_
     lp.hash_max_nnz = P->opts.hash_max_nnz;
     if (m > 0) {
         SPG_TRY(launch(P, "rowinfo", [&] {
-            k_rowinfo<<<rowinfo_grid(m), 256, 0, cs(P)>>>(a, b, k_lo, k_hi, full, bp, o);
+            k_rowinfo<<<rowinfo_grid(m), CLASS_NT, 0, cs(P)>>>(a, b, k_lo, k_hi, full, bp, o);
         }));
-        SPG_TRY(launch(P, "rowinfo_long", [&] {
-            k_rowinfo_long<<<256, 256, 0, cs(P)>>>(a, b, k_lo, k_hi, full, bp, o);
-        }));
-        SPG_TRY(fill_i64(P, stats, 4 * NBINS, 0));
         SPG_TRY(launch(P, "learned_classify", [&] {
             k_learned_classify<<<grid_for(m, 256), 256, 0, cs(P)>>>(m, n, mlp_params, lp, bp, P->a_beg.as<int64_t>(),
                                                                     P->a_end.as<int64_t>(), P->flops.as<int64_t>(),
                                                                     P->maxb.as<int32_t>(), P->bin.as<uint8_t>(),
-                                                                    P->lcap.as<int64_t>(), cnt, stats);
+                                                                    P->lcap.as<int64_t>(), cnt, stats, lorder);
         }));
         SPG_TRY(launch(P, "bin_scatter", [&] {
-            k_bin_scatter<<<grid_for(m, 256), 256, 0, cs(P)>>>(m, P->bin.as<uint8_t>(), stats, ctr + 2,
-                                                               P->lists.as<int32_t>());
+            k_bin_scatter<<<grid_for(m, CLASS_NT), CLASS_NT, 0, cs(P)>>>(m, P->bin.as<uint8_t>(), stats, lorder,
+                                                                         ctr + CTR_NUM_CURSOR, P->lists.as<int32_t>(),
+                                                                         stats, 0, nullptr);
         }));
         HIP_TRY(hipMemcpyAsync(P->slot.as<int64_t>() + 1, P->lcap.p, 8 * (size_t)m, hipMemcpyDeviceToDevice, cs(P)));
     }

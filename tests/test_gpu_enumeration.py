@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1510_00844_amd as spg
 from gpu_util import check_full_vs_oracle, to_dev
 from synth.gen import canonical_from_coo
@@ -102,4 +103,36 @@ def test_restriction_row_lengths(sizes):
     assert np.array_equal(R.col.cpu().numpy(), agg)
     with pytest.raises(spg.SpgError):
         spg.spg_restriction(plan, "i64", torch.zeros(4097, dtype=torch.int32, device="cuda"), 1)
+    plan.close()
+
+
+@pytest.mark.parametrize("window", [None, (100, 5900)])
+@pytest.mark.parametrize("reps", [1, 90])
+def test_row_analysis_lengths(window, reps):
+    """Rows around the lengths where the row analysis changes hands (16 lanes
+    per row to 128 entries, a wave to 2048, the workgroup above), the row
+    pointers and lists of more than one 1024-row tile, and the bin statistics."""
+    k, n = 6000, 700
+    counts = np.tile([0, 1, 15, 16, 17, 32, 33, 127, 128, 129, 300, 2047, 2048, 2049, 5000], reps)
+    rng = np.random.default_rng(2)
+    order = np.argsort(rng.random((64, k)), axis=1)
+    rows = np.repeat(np.arange(counts.size), counts)
+    cols = np.concatenate([order[i % 64, :c] for i, c in enumerate(counts)])
+    A = canonical_from_coo(counts.size, k, rows, cols, rng.integers(-5, 6, rows.size), dup="first")
+    blen = rng.choice([0, 1, 2, 40], k, p=[0.5, 0.3, 0.19, 0.01])
+    B = canonical_from_coo(k, n, np.repeat(np.arange(k), blen), np.concatenate([rng.choice(n, c, replace=False) for c in blen]),
+                           rng.integers(-5, 6, int(blen.sum())), dup="first")
+    plan = spg.Plan()
+    lo, hi = window or (None, None)
+    a, b = to_dev(A, "i64"), to_dev(B, "i64")
+    for _ in range(2):
+        C = spg.spgemm(plan, "i64", a, b, lo, hi)
+        check_full_vs_oracle(C, A, B, "i64", lo, hi)
+    st = plan.stats()
+    flops = oracle.row_flops(A, B, lo, hi)
+    assert st["flops"] == flops.sum() and st["nnz_c"] == C.nnz
+    assert sum(st["sym_rows"]) == sum(st["num_rows"]) == A.nrows
+    assert sum(st["num_flops"]) == flops.sum() and sum(st["num_cnnz"]) == C.nnz
+    inside = (A.col >= (lo or 0)) & (A.col < (k if hi is None else hi))
+    assert sum(st["sym_annz"]) == sum(st["num_annz"]) == int(inside.sum())
     plan.close()
