@@ -208,6 +208,19 @@ __device__ inline T wave_inclusive_scan_add(T v) {
     }
 }
 
+// Inclusive prefix maximum over the wave of values >= 0, in the same steps
+// (sources outside a row read 0).
+__device__ inline int32_t wave_inclusive_scan_max(int32_t x) {
+    auto mx = [](int32_t a, int32_t b) { return a > b ? a : b; };
+    x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true));   // row_shr:1
+    x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true));   // row_shr:2
+    x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true));   // row_shr:4
+    x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true));   // row_shr:8
+    x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return x;
+}
+
 // (The reductions keep ds_bpermute: with DPP steps the bitmap kernel's
 // per-chunk count loop ran 1.7x longer on 524288-column rows, measured.)
 template <typename T>

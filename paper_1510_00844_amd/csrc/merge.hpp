@@ -3,17 +3,15 @@
 // output is the sorted union of the c sorted segments layer_l(i,:), with
 // values of equal columns combined in ascending layer order.  The paper
 // merges with a heap per thread over a split of the column range; here:
-//   SORT   (more than 8 layers) rows of 65 ... MS_LMAX entries whose columns
-//          span less than 2^(32 - MS_XBITS): one wave per row; every entry
-//          becomes a 32-bit key (column - min, then its index in the
-//          layer-major order), the keys go to 64 column buckets (one per
-//          lane) and each lane sorts its bucket in registers; equal columns
-//          are then adjacent in ascending layer order
+//   SORT   (more than 4 layers) rows of 65 ... MS_LMAX entries whose columns
+//          span less than RS_SPAN_MAX: one wave per row sorts the entries
+//          by column and layer (rowsort.hpp) and folds equal columns in
+//          ascending layer order
 //   WAVE   rows of at most KW_LMAX entries over at most 8 layers: one
 //          wave per row, the column range split over the 64 lanes and each
 //          lane merging its range of the c segments (kway.hpp), staged in LDS
-//   SMALL  (more layers than the wave merge takes) rows of <= 64 entries:
-//          a wave sort of (column, position)
+//   SMALL  (more than 4 layers) rows of <= 64 entries: a wave sort of
+//          (column, position)
 //   RANK   65 ... 4096 entries: a workgroup places each entry by binary
 //          searches in the other layers' segments, staged in LDS
 //   DENSE  longer rows: a workgroup sweeping column chunks with an LDS dense
@@ -21,6 +19,7 @@
 //          column-range split of Section 4.3)
 #pragma once
 #include "kway.hpp"
+#include "rowsort.hpp"
 #include "products.hpp"
 #include "rowinfo.hpp"
 
@@ -44,31 +43,39 @@ constexpr int MBIN_EMPTY = 0, MBIN_WAVE = 1, MBIN_SMALL = 2, MBIN_R256 = 3, MBIN
               MBIN_DENSE = 6, MBIN_SORT = 7;
 constexpr int MBINS = 8;
 
-// the bucket-sort bin: entries per row, bits of a staged index, column span
-constexpr int MS_LMAX = 512;
-constexpr int MS_XBITS = 9;
-constexpr int64_t MS_SPAN_MAX = 1ll << (32 - MS_XBITS);
-static_assert((MS_LMAX & (MS_LMAX - 1)) == 0 && MS_LMAX <= (1 << MS_XBITS),
-              "the whole-row sort pads to a power of two inside the key array");
+// the SORT bin's rows
+constexpr int MS_LMAX = RS_MAX;
+constexpr int64_t MS_SPAN_MAX = RS_SPAN_MAX;
 constexpr int MERGE_LDS_MAX = 4096;
 
-// The wave k-way merge costs O(c) instructions per output (the smallest of c
-// heads each step): it wins for few layers (with 4 layers it is 1.6 times
-// as fast as the bucket sort); more layers take the bucket sort and rank
-// paths.
+// layers the wave k-way merge takes (it costs O(c) instructions per output)
 constexpr int MERGE_KWAY_MAX_LAYERS = 8;
+
+// Rows whose columns pack (see RS_SPAN_MAX) are sorted from five layers on: the
+// cost of the k-way sweep grows with the layers (ER scale 18, 256 entries a row,
+// count and fill: two layers 0.93 ms by either, four 1.06 against 1.00 by the
+// sort, eight 1.52 against 1.02).  At three and four layers the sort's lead is
+// lost on rows of mixed lengths, where it needs bins of its own (SSCA scale 15,
+// four layers: 0.33 against 0.29).  Rows of up to 64 entries take the register
+// sort (25 entries a row, eight layers: 0.30 against 0.38 by the sweep).
+__device__ inline int64_t merge_sort_min(int c) {  // rows of more entries are sorted
+    return c <= 4 ? MS_LMAX : SPG_WAVE;
+}
 
 __device__ inline int merge_bin(int64_t L, int c) {
     if (L == 0) return MBIN_EMPTY;
+    if (L <= SPG_WAVE && c > 4) return MBIN_SMALL;
     if (L <= KW_LMAX && c <= MERGE_KWAY_MAX_LAYERS) return MBIN_WAVE;
-    if (L <= SPG_WAVE) return MBIN_SMALL;
     if (L <= 256) return MBIN_R256;
     if (L <= 1024) return MBIN_R1K;
     if (L <= MERGE_LDS_MAX) return MBIN_R4K;
     return MBIN_DENSE;
 }
 
-__global__ void __launch_bounds__(256) k_merge_rowinfo(int64_t m, int32_t c, LayerSet layers,
+// packs: every span of the n columns packs (n <= MS_SPAN_MAX), so no column is
+// read (the two ends of every segment were most of this kernel's time: 67 -> 28
+// us for 16 layers of 262,144 rows).
+__global__ void __launch_bounds__(256) k_merge_rowinfo(int64_t m, int32_t c, LayerSet layers, int packs,
                                                        int64_t* total_len, uint8_t* bin,
                                                        int64_t* bin_stats) {
     __shared__ int s_hist[NBINS];
@@ -83,9 +90,9 @@ __global__ void __launch_bounds__(256) k_merge_rowinfo(int64_t m, int32_t c, Lay
         for (int l = 0; l < c; ++l) L += layers.d[l].rp[i + 1] - layers.d[l].rp[i];
         total_len[i] = L;
         int b = merge_bin(L, c);
-        if (c > MERGE_KWAY_MAX_LAYERS && L > SPG_WAVE && L <= MS_LMAX) {  // the bucket sort, if the columns pack
-            int32_t mn = 0x7fffffff, mx = -1;
-            for (int l = 0; l < c; ++l) {
+        if (L > merge_sort_min(c) && L <= MS_LMAX) {  // the bucket sort, if the columns pack
+            int32_t mn = packs ? 0 : 0x7fffffff, mx = packs ? 0 : -1;
+            for (int l = 0; l < c && !packs; ++l) {
                 const int64_t rs = layers.d[l].rp[i], re = layers.d[l].rp[i + 1];
                 if (re > rs) {
                     const int32_t a = layers.d[l].col[rs], z = layers.d[l].col[re - 1];
@@ -136,6 +143,63 @@ __global__ void __launch_bounds__(256) k_merge_kway(int32_t c, LayerSet layers, 
     }
 }
 
+// The flat order of a merge row (layer 0's segment, then layer 1's, ...) over
+// a wave: lane l < c holds layer l's segment; entry x of the flat order lies in
+// the last non-empty layer that starts at or before it.
+struct MergeRow {
+    int32_t off;          // first entry of the lane's layer
+    int32_t L;            // entries (wave-uniform)
+    const int32_t* colp;  // entry x of the layer: colp[x], valp[x]
+    int64_t rel;          // ... = arrays of the layer at rel + x
+    const void* valp;
+};
+__device__ inline MergeRow merge_row(const LayerSet& layers, int32_t c, int64_t i) {
+    const int lane = lane_id();
+    MergeRow m{0, 0, nullptr, 0, nullptr};
+    int64_t rs = 0;
+    int32_t len = 0;
+    if (lane < c) {
+        rs = layers.d[lane].rp[i];
+        len = (int32_t)(layers.d[lane].rp[i + 1] - rs);
+        m.colp = layers.d[lane].col;
+        m.valp = layers.d[lane].val;
+    }
+    const int32_t incl = wave_inclusive_scan_add(len);
+    m.off = len > 0 ? incl - len : -1;  // (empty layers own no entry)
+    m.L = __builtin_amdgcn_readlane(incl, SPG_WAVE - 1);
+    m.rel = rs - (incl - len);
+    if (m.colp) m.colp += m.rel;
+    return m;
+}
+// Layer of entry x = u * 64 + lane of each step: the lane of every non-empty
+// layer is marked (a byte; NU * 64 of them in the wave's LDS) at its first
+// entry, and a running maximum of the marks gives each entry its layer (a
+// search over the layers took log2(c) lane exchanges a step).
+template <int NU>
+__device__ inline void merge_layers_of(const MergeRow& m, uint8_t* marks, int32_t (&l)[NU]) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int t = 0; t < NU / 4; ++t)
+        if (t * 4 * SPG_WAVE < m.L) reinterpret_cast<uint32_t*>(marks)[t * SPG_WAVE + lane] = 0;
+    wave_lds_sync();
+    if (m.off >= 0) marks[m.off] = (uint8_t)lane;
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        if (u * SPG_WAVE >= m.L) break;
+        l[u] = marks[u * SPG_WAVE + lane];
+    }
+    int32_t carry = 0;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        if (u * SPG_WAVE >= m.L) break;
+        const int32_t x = wave_inclusive_scan_max(l[u]);
+        l[u] = x > carry ? x : carry;
+        carry = __builtin_amdgcn_readlane(l[u], SPG_WAVE - 1);
+    }
+    wave_lds_sync();  // the marks are read before their bytes are used again
+}
+
 // Count pass of the WAVE and SORT bins (rows of at most MS_LMAX entries):
 // counting needs no order, so the row's columns are inserted into an LDS
 // hash set of MC_SLOTS slots (at most half full), one wave per row, and
@@ -148,6 +212,7 @@ static_assert(MC_SLOTS >= 2 * MS_LMAX && MS_LMAX >= KW_LMAX, "the hash count tak
 __global__ void __launch_bounds__(256) k_merge_count_hash(int32_t c, LayerSet layers, BinRef ref, int64_t* cnt) {
     constexpr int NU = MS_LMAX / SPG_WAVE;
     __shared__ int32_t tab[4][MC_SLOTS];
+    __shared__ __align__(4) uint8_t marks[4][MS_LMAX];
     int32_t* T = tab[threadIdx.x >> 6];
     const int lane = lane_id();
     for (int t = lane; t < MC_SLOTS; t += SPG_WAVE) T[t] = -1;
@@ -155,49 +220,35 @@ __global__ void __launch_bounds__(256) k_merge_count_hash(int32_t c, LayerSet la
     const int32_t* rows;
     int64_t n;
     ref.locate(rows, n);
-    int top = 1;  // search width over the layers
-    while (top < c) top <<= 1;
     for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n; r += (int64_t)gridDim.x * 4) {
         const int64_t i = rows[r];
-        int64_t rs = 0;
-        int32_t len = 0;
-        const int32_t* colp = nullptr;
-        if (lane < c) {
-            colp = layers.d[lane].col;
-            rs = layers.d[lane].rp[i];
-            len = (int32_t)(layers.d[lane].rp[i + 1] - rs);
-        }
-        const int32_t incl = wave_inclusive_scan_add(len);
-        const int32_t soff = incl - len;
-        const int32_t L = __builtin_amdgcn_readlane(incl, SPG_WAVE - 1);
+        const MergeRow m = merge_row(layers, c, i);
+        const int32_t L = m.L;
+        int32_t l[NU], col[NU], used[NU];
+        merge_layers_of<NU>(m, marks[threadIdx.x >> 6], l);
         int32_t mine = 0;
-        int32_t used[NU];
 #pragma unroll
-        for (int u = 0; u < NU; ++u) used[u] = -1;
+        for (int u = 0; u < NU; ++u) {
+            used[u] = -1;
+            if (u * SPG_WAVE >= L) break;
+            const int32_t x = u * SPG_WAVE + lane;
+            const int32_t* cp = (const int32_t*)(intptr_t)lane_get((int64_t)(intptr_t)m.colp, l[u]);
+            col[u] = cp[x < L ? x : L - 1];
+        }
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             if (u * SPG_WAVE >= L) break;
-            const int32_t x = u * SPG_WAVE + lane;
-            int l = 0;
-            for (int step = top >> 1; step > 0; step >>= 1) {
-                const int cand = l + step;
-                const int32_t so = __shfl(soff, cand < SPG_WAVE ? cand : SPG_WAVE - 1, SPG_WAVE);
-                if (cand < c && so <= x) l = cand;
-            }
-            const int32_t lo = __shfl(soff, l, SPG_WAVE);
-            const int64_t st = __shfl((long long)rs, l, SPG_WAVE);
-            const int32_t* cp = (const int32_t*)__shfl((long long)(intptr_t)colp, l, SPG_WAVE);
-            if (x < L) {
-                const int32_t col = cp[st + (x - lo)];
-                uint32_t h = hash_slot(col, MC_LOG2);
+            pin(col[u]);
+            if (u * SPG_WAVE + lane < L) {
+                uint32_t h = hash_slot(col[u], MC_LOG2);
                 while (true) {  // ends: the set is at most half full
-                    const int32_t old = atomicCAS(&T[h], -1, col);
+                    const int32_t old = atomicCAS(&T[h], -1, col[u]);
                     if (old == -1) {
                         ++mine;
                         used[u] = (int32_t)h;
                         break;
                     }
-                    if (old == col) break;
+                    if (old == col[u]) break;
                     h = (h + 1) & (MC_SLOTS - 1);
                 }
             }
@@ -206,160 +257,80 @@ __global__ void __launch_bounds__(256) k_merge_count_hash(int32_t c, LayerSet la
         if (lane == 0) cnt[i] = tot;
         wave_lds_sync();  // every insertion is done before the set is cleared
 #pragma unroll
-        for (int u = 0; u < NU; ++u)
+        for (int u = 0; u < NU; ++u) {
+            if (u * SPG_WAVE >= L) break;
             if (used[u] >= 0) T[used[u]] = -1;
+        }
         wave_lds_sync();
     }
 }
 
-// Per-wave LDS of the bucket-sort merge: the row's keys, its values by
-// staged index (fill pass), the bucket counters.
-template <typename V, bool FILL>
-struct MsLds {
-    uint32_t key[MS_LMAX];
-    V val[FILL ? MS_LMAX : 1];
-    int32_t bcnt[SPG_WAVE];
-};
-
-// One wave per row of the SORT bin (4 per workgroup).  Entry x of the flat
-// order (layer 0's segment, then layer 1's, ...) gets the key
-// (column - cmin) << MS_XBITS | x, so keys order by column and equal columns
-// by layer.  The keys are counted into 64 buckets of equal column width
-// (bucket = (column - cmin) * 64 / span in FP32, monotone), placed bucket by
-// bucket, and every lane sorts its own bucket with a register network; a
-// row whose largest bucket holds more than 16 is sorted whole by the wave
-// (a larger network would cost registers, and so waves, on every row).
-// Runs of equal columns are then folded in key order.  cnt != nullptr: count
-// pass; otherwise fill pass at out_rp.
-template <int SR, bool FILL>
-__global__ void __launch_bounds__(256) k_merge_sort(int32_t c, LayerSet layers, BinRef ref, int64_t* cnt,
-                                                    const int64_t* out_rp, int32_t* out_col, void* out_val) {
+// One wave per row of the SORT bin (4 per workgroup): the row's entries in the
+// flat order (equal columns in ascending layer order), sorted and folded by
+// rowsort.hpp, its columns and values four steps in flight.  Bound by latency
+// at 5 waves per SIMD: the register limit of launch bounds (96 instead of 108,
+// no spill) took the 16-layer merge from 1.17 to 1.06 ms; 80 registers spill
+// and take 1.12.
+template <int SR>
+__global__ void __launch_bounds__(256, 5) k_merge_sort(int32_t c, LayerSet layers, BinRef ref, const int64_t* out_rp,
+                                                    int32_t* out_col, void* out_val) {
     typedef Sr<SR> S;
     typedef typename S::acc_t V;
     constexpr int NU = MS_LMAX / SPG_WAVE;
-    constexpr uint32_t XMASK = (1u << MS_XBITS) - 1;
-    __shared__ MsLds<V, FILL> lds[4];
-    MsLds<V, FILL>& W = lds[threadIdx.x >> 6];
+    __shared__ RowSortLds<V, NU> lds[4];
+    RowSortLds<V, NU>& W = lds[threadIdx.x >> 6];
     const int32_t* rows;
     int64_t n;
     ref.locate(rows, n);
     const int lane = lane_id();
-    int top = 1;  // search width over the layers
-    while (top < c) top <<= 1;
     for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n; r += (int64_t)gridDim.x * 4) {
         const int64_t i = rows[r];
-        // lane l < c: layer l's segment, its first and last column
-        int64_t rs = 0;
-        int32_t len = 0, cmin = 0x7fffffff, cmax = -1;
-        const int32_t* colp = nullptr;
-        const void* valp = nullptr;
-        if (lane < c) {
-            colp = layers.d[lane].col;
-            valp = layers.d[lane].val;
-            rs = layers.d[lane].rp[i];
-            len = (int32_t)(layers.d[lane].rp[i + 1] - rs);
-            if (len > 0) {
-                cmin = colp[rs];
-                cmax = colp[rs + len - 1];
+        const MergeRow m = merge_row(layers, c, i);
+        const int32_t L = m.L;
+        const int64_t o = out_rp[i];
+        const int32_t room = (int32_t)(out_rp[i + 1] - o);
+        int32_t l[NU], col[NU];
+        merge_layers_of<NU>(m, reinterpret_cast<uint8_t*>(W.key), l);
+        W.bcnt[lane] = 0;
+        constexpr int U = 4;
+#pragma unroll
+        for (int u0 = 0; u0 < NU; u0 += U) {
+            if (u0 * SPG_WAVE >= L) break;
+            V v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if ((u0 + u) * SPG_WAVE >= L) break;
+                const int32_t x = (u0 + u) * SPG_WAVE + lane;
+                const int32_t y = x < L ? x : L - 1;
+                const int32_t* cp = (const int32_t*)(intptr_t)lane_get((int64_t)(intptr_t)m.colp, l[u0 + u]);
+                const void* vp = (const void*)(intptr_t)lane_get((int64_t)(intptr_t)m.valp, l[u0 + u]);
+                col[u0 + u] = cp[y];
+                // no value array: structure-only output (booleans: all true)
+                v[u] = S::zero();
+                if (vp) v[u] = S::load(vp, lane_get(m.rel, l[u0 + u]) + y);
+                else if (SR == SR_BOOL) v[u] = S::load(nullptr, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if ((u0 + u) * SPG_WAVE >= L) break;
+                pin(col[u0 + u]);
+                pin(v[u]);
+                const int32_t x = (u0 + u) * SPG_WAVE + lane;
+                if (x < L) W.val[x] = v[u];
             }
         }
-        const int32_t incl = wave_inclusive_scan_add(len);
-        const int32_t soff = incl - len;
-        const int32_t L = __builtin_amdgcn_readlane(incl, SPG_WAVE - 1);
-#pragma unroll
-        for (int d = SPG_WAVE / 2; d > 0; d >>= 1) {
-            const int32_t a = lane_xor(cmin, d), b = lane_xor(cmax, d);
-            cmin = a < cmin ? a : cmin;
-            cmax = b > cmax ? b : cmax;
-        }
-        const float bscale = (float)SPG_WAVE / (float)((int64_t)cmax - cmin + 1);
-        W.bcnt[lane] = 0;
-        wave_lds_sync();
-        // stage: entry x = u * 64 + lane lies in the last layer whose
-        // segment starts at or before x (empty segments share the start of
-        // the next one)
-        uint32_t ck[NU];
-        int32_t cbs[NU];  // bucket << 16 | place in the bucket
+        int32_t cmin = 0x7fffffff, cmax = -1;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             if (u * SPG_WAVE >= L) break;
-            const int32_t x = u * SPG_WAVE + lane;
-            int l = 0;
-            for (int step = top >> 1; step > 0; step >>= 1) {
-                const int cand = l + step;
-                const int32_t so = __shfl(soff, cand < SPG_WAVE ? cand : SPG_WAVE - 1, SPG_WAVE);
-                if (cand < c && so <= x) l = cand;
-            }
-            const int32_t lo = __shfl(soff, l, SPG_WAVE);
-            const int64_t st = __shfl((long long)rs, l, SPG_WAVE);
-            const int32_t* cp = (const int32_t*)__shfl((long long)(intptr_t)colp, l, SPG_WAVE);
-            const void* vp = FILL ? (const void*)__shfl((long long)(intptr_t)valp, l, SPG_WAVE) : nullptr;
-            if (x < L) {
-                const int64_t q = st + (x - lo);
-                const uint32_t rel = (uint32_t)(cp[q] - cmin);
-                int32_t b = (int32_t)((float)rel * bscale);
-                b = b < SPG_WAVE - 1 ? b : SPG_WAVE - 1;
-                ck[u] = (rel << MS_XBITS) | (uint32_t)x;
-                cbs[u] = (b << 16) | atomicAdd(&W.bcnt[b], 1);
-                if constexpr (FILL) {
-                    // no value array: structure-only output (booleans: all true)
-                    W.val[x] = (vp || SR == SR_BOOL) ? S::load(vp, q) : S::zero();
-                }
-            }
+            cmin = col[u] < cmin ? col[u] : cmin;
+            cmax = col[u] > cmax ? col[u] : cmax;
         }
+        cmin = __builtin_amdgcn_readfirstlane(wave_all(cmin, [](int32_t x, int32_t y) { return x < y ? x : y; }));
+        cmax = __builtin_amdgcn_readfirstlane(wave_all(cmax, [](int32_t x, int32_t y) { return x > y ? x : y; }));
         wave_lds_sync();
-        const int32_t mycnt = W.bcnt[lane];
-        const int32_t bmax = wave_reduce_max(mycnt);
-        const int32_t boff = wave_inclusive_scan_add(mycnt) - mycnt;
-        wave_lds_sync();  // every lane has read its count
-        W.bcnt[lane] = boff;
-        wave_lds_sync();
-        if (bmax <= 16) {
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                if (u * SPG_WAVE >= L) break;
-                if (u * SPG_WAVE + lane < L) W.key[W.bcnt[cbs[u] >> 16] + (cbs[u] & 0xffff)] = ck[u];
-            }
-            wave_lds_sync();
-            if (bmax <= 8) bucket_sort_net<8>(W.key, boff, mycnt, MS_LMAX);
-            else bucket_sort_net<16>(W.key, boff, mycnt, MS_LMAX);
-        } else {
-            int P = SPG_WAVE;
-            while (P < L) P <<= 1;
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const int32_t x = u * SPG_WAVE + lane;
-                if (x < L) W.key[x] = ck[u];
-                else if (x < P) W.key[x] = 0xffffffffu;
-            }
-            wave_lds_sync();
-            wave_lds_bitonic_u32(W.key, P);
-        }
-        wave_lds_sync();
-        // runs of equal columns: each lane takes a contiguous range of
-        // sorted positions and owns the runs that start there
-        const int per = (L + SPG_WAVE - 1) / SPG_WAVE;
-        const int q0 = lane * per < L ? lane * per : L;
-        const int q1 = q0 + per < L ? q0 + per : L;
-        int32_t heads = 0;
-        for (int q = q0; q < q1; ++q) heads += (q == 0 || (W.key[q] >> MS_XBITS) != (W.key[q - 1] >> MS_XBITS)) ? 1 : 0;
-        if constexpr (!FILL) {
-            const int32_t tot = wave_reduce_add(heads);
-            if (lane == 0) cnt[i] = tot;
-        } else {
-            int64_t o = out_rp[i] + (wave_inclusive_scan_add(heads) - heads);
-            for (int q = q0; q < q1; ++q) {
-                const uint32_t kq = W.key[q];
-                if (q == 0 || (kq >> MS_XBITS) != (W.key[q - 1] >> MS_XBITS)) {
-                    V acc = W.val[kq & XMASK];
-                    for (int y = q + 1; y < L && (W.key[y] >> MS_XBITS) == (kq >> MS_XBITS); ++y)
-                        acc = S::add(acc, W.val[W.key[y] & XMASK]);
-                    out_col[o] = cmin + (int32_t)(kq >> MS_XBITS);
-                    if (out_val) S::store(out_val, o, acc);
-                    ++o;
-                }
-            }
-        }
+        wave_sort_row(W, L, cmin, cmax, col);
+        (void)wave_fold_row<SR, NU>(W, L, cmin, out_col, out_val, o, room);
         wave_lds_sync();  // the row's LDS is read before the next row overwrites it
     }
 }

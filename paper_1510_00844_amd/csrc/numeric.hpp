@@ -5,7 +5,9 @@
 //   SMALL  <= 64 products: one wave per row; products sorted across the wave
 //          by (column, product order), equal columns folded left to right,
 //          which is ascending k (the order of Algorithm 1)
-//   HASH   workgroup per row: LDS open-addressing table sized >= 4/3 slots per
+//   HASH   rows of few products per output in the bins of up to 384 outputs: a
+//          wave sorts the products (rowsort.hpp); otherwise
+//          workgroup per row: LDS open-addressing table sized >= 4/3 slots per
 //          output, semiring add by LDS atomics, then compaction and an LDS
 //          bitonic sort by column
 //   RANK   rows whose symbolic pass kept an n-bit bitmap: the bitmap is
@@ -20,6 +22,7 @@
 #pragma once
 #include "products.hpp"
 #include "rowinfo.hpp"
+#include "rowsort.hpp"
 #include "symbolic.hpp"
 
 namespace spg {
@@ -150,30 +153,133 @@ __global__ void __launch_bounds__(256) k_num_small(Csr A, Csr B, const int32_t* 
     }
 }
 
+// A row of the one-wave hash bins by sorting (rowsort.hpp): f products, at
+// most 64 NU.  Each batch of 64 A entries is scanned, the lane of every
+// non-empty B segment is marked at its first product, and a running maximum of
+// the marks gives each product its segment.
+template <int SR, int NU>
+__device__ inline void num_sort_row(const Csr& A, const Csr& B, int64_t beg, int64_t end, int32_t f,
+                                    RowSortLds<typename Sr<SR>::acc_t, NU>& W, uint8_t* marks, int32_t* c_col,
+                                    void* c_val, int64_t o, int32_t room) {
+    typedef Sr<SR> S;
+    typedef typename S::acc_t V;
+    const int lane = lane_id();
+    int32_t pos = 0;  // products of the batches before
+    for (int64_t base = beg; base < end && pos < f; base += SPG_WAVE) {
+        const int64_t p = base + lane;
+        int64_t bs = 0;
+        int32_t len = 0;
+        V av = S::zero();
+        if (p < end) {
+            const int64_t k = A.col[p];
+            bs = B.rp[k];
+            len = (int32_t)(B.rp[k + 1] - bs);
+            av = S::load(A.val, p);
+        }
+        const int32_t inc = wave_inclusive_scan_add(len);
+        int32_t nb = __builtin_amdgcn_readlane(inc, SPG_WAVE - 1);
+        nb = nb < f - pos ? nb : f - pos;  // (f counts them all: a guard for inputs changed since)
+        const int32_t off = inc - len;
+        const int64_t rel = bs - off;
+#pragma unroll
+        for (int t = 0; t < NU / 4 + 1; ++t)
+            if (t * SPG_WAVE + lane < NU * SPG_WAVE / 4) reinterpret_cast<uint32_t*>(marks)[t * SPG_WAVE + lane] = 0;
+        wave_lds_sync();
+        if (len > 0 && off < nb) marks[off] = (uint8_t)lane;
+        wave_lds_sync();
+        // four steps of gathers in flight (more cost registers, so waves)
+        constexpr int U = NU < 4 ? NU : 4;
+        int32_t carry = 0;
+#pragma unroll
+        for (int u0 = 0; u0 < NU; u0 += U) {
+            if (u0 * SPG_WAVE >= nb) break;
+            int32_t mark[U];
+            V a[U];
+            BEntry<V> e[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t x = (u0 + u) * SPG_WAVE + lane;
+                mark[u] = marks[x < nb ? x : nb - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int32_t l = wave_inclusive_scan_max(mark[u]);
+                l = l > carry ? l : carry;
+                carry = __builtin_amdgcn_readlane(l, SPG_WAVE - 1);
+                const int32_t x = (u0 + u) * SPG_WAVE + lane;
+                const int64_t q = lane_get(rel, l) + (x < nb ? x : nb - 1);
+                a[u] = lane_get(av, l);
+                e[u] = BEntry<V>{B.col[q], S::load(B.val, q)};
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                pin(e[u]);
+                const int32_t x = (u0 + u) * SPG_WAVE + lane;
+                if (x < nb) {
+                    W.key[pos + x] = (uint32_t)e[u].col;
+                    W.val[pos + x] = S::mul(a[u], e[u].val);
+                }
+            }
+        }
+        pos += nb;
+        wave_lds_sync();
+    }
+    if (pos == 0) return;
+    int32_t col[NU], cmin, cmax;
+    wave_row_span(W, pos, col, cmin, cmax);
+    wave_sort_row(W, pos, cmin, cmax, col);
+    (void)wave_fold_row<SR, NU>(W, pos, cmin, c_col, c_val, o, room);
+}
+
 // cnt_out (optional) receives each row's output count; a count above the
 // slot c_rp.count(i) means the slot overflowed (only then is the output
 // incomplete).
 template <int SR, int NT, int LOG2T>
 __global__ void __launch_bounds__(NT) k_num_hash(Csr A, Csr B, const int32_t* rows,
                                                  const int64_t* a_beg, const int64_t* a_end,
-                                                 OutRows c_rp, int32_t* c_col, void* c_val,
+                                                 const int64_t* flops, OutRows c_rp, int32_t* c_col, void* c_val,
                                                  int64_t* cnt_out) {
     typedef Sr<SR> S;
     typedef typename S::acc_t V;
     constexpr int T = 1 << LOG2T;
     constexpr int PER = T / NT;  // table slots owned by a thread during compaction
     static_assert(PER >= 1, "table smaller than block");
-    __shared__ int32_t tkey[T];
     // 8 bytes a slot whatever the value type: the full sort below keeps up
     // to T keys of 8 bytes there
-    __shared__ uint64_t tval_store[T];
+    struct Table {
+        uint64_t val[T];
+        int32_t key[T];
+    };
+    constexpr bool SORT = NT == SPG_WAVE;  // the one-wave bins sort most rows instead
+    // steps of 64 products a row may sort (256 in the smallest bin: Galerkin
+    // rows of 140 products have 65 outputs)
+    constexpr int NU = !SORT ? 1 : (T < 4 * SPG_WAVE ? 4 : T / SPG_WAVE);
+    union Lds {
+        Table table;
+        RowSortLds<V, NU> sort;
+        __device__ Lds() {}
+    };
+    __shared__ Lds lds;
+    int32_t* tkey = lds.table.key;
+    uint64_t* tval_store = lds.table.val;
     V* tval = reinterpret_cast<V*>(tval_store);
     __shared__ ProductLds<NT> L;
     __shared__ int32_t red[NT / SPG_WAVE + 1];
     __shared__ int32_t mm[2 * (NT / SPG_WAVE)];
     __shared__ V s_av[NT];
     __shared__ int32_t s_bucket[NT];
+    __shared__ __align__(4) uint8_t s_mark[SORT ? (T > 4 * SPG_WAVE ? T : 4 * SPG_WAVE) : 4];
     const int64_t i = rows[blockIdx.x];
+    if constexpr (SORT) {
+        // sorting costs by the product, the table by the slot and the output:
+        // rows of up to 64 NU products and four per output are sorted
+        const int64_t f = flops[i], n = c_rp.count(i);
+        if (!cnt_out && f <= NU * SPG_WAVE && f <= 4 * n && B.ncols <= RS_SPAN_MAX) {
+            num_sort_row<SR, NU>(A, B, a_beg[i], a_end[i], (int32_t)f, lds.sort, s_mark, c_col, c_val, c_rp.off(i),
+                                 (int32_t)n);
+            return;
+        }
+    }
     for (int t = threadIdx.x; t < T; t += NT) {
         tkey[t] = EMPTY_KEY;
         tval[t] = S::zero();
@@ -200,7 +306,7 @@ __global__ void __launch_bounds__(NT) k_num_hash(Csr A, Csr B, const int32_t* ro
     if constexpr (NT == SPG_WAVE) {
         // one wave: the lane search needs no block-wide enumeration
         wave_products<4, V>(
-            a_beg[i], a_end[i],
+            a_beg[i], a_end[i], s_mark,
             [&](int64_t p, int64_t& bs, int32_t& len, V& av) {
                 const int64_t k = A.col[p];
                 bs = B.rp[k];

@@ -337,13 +337,15 @@ __device__ inline void for_each_product_gm(int64_t a_beg, int64_t a_end, Product
 // whose B rows are short (no workgroup-wide enumeration, no barriers).  The
 // row's A entries are taken 64 at a time: seg(p, bs, len, pa) gives lane
 // p - base its B segment and a per-entry payload pa (the A value); a wave
-// scan of the lengths gives the segment offsets, and product x of the batch
-// (x = 64 (U s + u) + lane) lies in the last lane's segment starting at or
-// before x (a binary search across the lanes; empty segments share the
-// start of the next one).  Each lane issues its U gathers (load(q)) before
-// applying any (apply(pa, x)), so U loads are in flight.
+// scan of the lengths gives the segment offsets.  The products are taken in
+// rounds of U steps of 64: the lane of every non-empty segment is marked in
+// LDS (64 U bytes of the wave's own) at the segment's first product of the
+// round, and a running maximum of the marks over the round gives each product
+// its segment (a binary search across the lanes took six exchanges a step).
+// Each lane issues its U gathers (load(q)) before applying any (apply(pa, x)),
+// so U loads are in flight.
 template <int U, typename PA, class Seg, class Load, class Apply>
-__device__ inline void wave_products(int64_t beg, int64_t end, Seg seg, Load load, Apply apply) {
+__device__ inline void wave_products(int64_t beg, int64_t end, uint8_t* marks, Seg seg, Load load, Apply apply) {
     typedef decltype(load((int64_t)0)) X;
     const int lane = lane_id();
     for (int64_t base = beg; base < end; base += SPG_WAVE) {
@@ -353,32 +355,40 @@ __device__ inline void wave_products(int64_t beg, int64_t end, Seg seg, Load loa
         PA pa{};
         if (p < end) seg(p, bs, len, pa);
         const int32_t incl = wave_inclusive_scan_add(len);
-        const int32_t soff = incl - len;
+        const int32_t off = incl - len;
+        const int64_t rel = bs - off;
         const int32_t nb = __builtin_amdgcn_readlane(incl, SPG_WAVE - 1);
         for (int32_t x0 = 0; x0 < nb; x0 += SPG_WAVE * U) {
-            int64_t q[U];
+            static_assert(U == 4, "a word of marks per lane");
+            reinterpret_cast<uint32_t*>(marks)[lane] = 0;
+            wave_lds_sync();
+            // a segment that began before the round is marked at its start
+            const int32_t first = off > x0 ? off : x0;
+            if (first < incl && first < x0 + SPG_WAVE * U) marks[first - x0] = (uint8_t)lane;
+            wave_lds_sync();
+            int32_t m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) m[u] = marks[u * SPG_WAVE + lane];
+            wave_lds_sync();  // read before the next round clears them
             PA a[U];
-            bool ok[U];
+            X v[U];
+            int32_t carry = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                int32_t l = wave_inclusive_scan_max(m[u]);
+                l = l > carry ? l : carry;
+                carry = __builtin_amdgcn_readlane(l, SPG_WAVE - 1);
                 const int32_t x = x0 + u * SPG_WAVE + lane;
-                int l = 0;
-#pragma unroll
-                for (int step = SPG_WAVE / 2; step > 0; step >>= 1) {
-                    const int32_t so = __shfl(soff, l + step, SPG_WAVE);
-                    if (so <= x) l += step;
-                }
-                q[u] = lane_get(bs, l) + (x - __shfl(soff, l, SPG_WAVE));
+                // products past the batch load its last one and apply nothing
+                const int64_t q = lane_get(rel, l) + (x < nb ? x : nb - 1);
                 a[u] = lane_get(pa, l);
-                ok[u] = x < nb;
+                v[u] = load(q);
             }
-            X v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (ok[u]) v[u] = load(q[u]);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (ok[u]) apply(a[u], v[u]);
+            for (int u = 0; u < U; ++u) {
+                pin(v[u]);
+                if (x0 + u * SPG_WAVE + lane < nb) apply(a[u], v[u]);
+            }
         }
     }
 }

@@ -272,7 +272,6 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
         uint64_t longs[R];  // the wave's groups with a long row (a bit per lane of them)
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            if (active[u]) window(beg[u], end[u]);
             const bool is_long = end[u] - beg[u] > LONG_ROW;
             bool hub = false;
             if (is_long && gl == 0 && end[u] - beg[u] > HUB_ROW) {
@@ -288,6 +287,9 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
         int64_t most = 0;
 #pragma unroll
         for (int u = 0; u < R; ++u) most = active[u] && end[u] - beg[u] > most ? end[u] - beg[u] : most;
+        // the whole row is read and entries outside the window are dropped
+        // (two binary searches are a chain of dependent loads)
+        int32_t below[R] = {}, inside[R] = {};
         for (int64_t x = gl; x < most; x += G * E) {
             int64_t k[R][E], l0[R][E], l1[R][E];
 #pragma unroll
@@ -297,6 +299,16 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
                     const int64_t p = beg[u] + x + e * G;
                     k[u][e] = active[u] && p < end[u] ? (int64_t)A.col[p] : -1;
                 }
+            if (!full_window) {
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        below[u] += k[u][e] >= 0 && k[u][e] < k_lo;
+                        if (k[u][e] < k_lo || k[u][e] >= k_hi) k[u][e] = -1;
+                        inside[u] += k[u][e] >= 0;
+                    }
+            }
 #pragma unroll
             for (int u = 0; u < R; ++u)
 #pragma unroll
@@ -313,6 +325,20 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
                     mb[u] = l > mb[u] ? (int32_t)l : mb[u];
                 }
         }
+        if (!full_window) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+#pragma unroll
+                for (int d = G / 2; d > 0; d >>= 1) {
+                    below[u] += lane_xor(below[u], d);
+                    inside[u] += lane_xor(inside[u], d);
+                }
+                if (active[u]) {
+                    beg[u] += below[u];
+                    end[u] = beg[u] + inside[u];
+                }
+            }
+        }
 #pragma unroll
         for (int u = 0; u < R; ++u) {
             // reduce inside the 16-lane group (xor offsets < 16 stay in the group)
@@ -325,7 +351,8 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
             if (active[u] && gl == 0) finish(i0 + u * step + g, beg[u], end[u], f[u], mb[u]);
             for (uint64_t m = longs[u]; m; m &= m - 1) {
                 const int l = __builtin_ctzll(m);
-                const int64_t lb = lane_get(beg[u], l), le = lane_get(end[u], l);
+                int64_t lb = lane_get(beg[u], l), le = lane_get(end[u], l);
+                window(lb, le);
                 int64_t lf;
                 int32_t lm;
                 walk_entries(A, B, lb, le, lane, SPG_WAVE, lf, lm);

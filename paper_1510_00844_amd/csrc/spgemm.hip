@@ -1155,7 +1155,8 @@ static spg_status launch_num_hash(spg_plan P, Csr A, Csr B, const int32_t* rows,
     const int64_t* ab = P->a_beg.as<int64_t>();
     const int64_t* ae = P->a_end.as<int64_t>();
     return launch(P, "num_hash" + std::to_string(1 << LOG2T), [&] {
-        k_num_hash<SR, NT, LOG2T><<<(unsigned)nr, NT, 0, cs(P)>>>(A, B, rows, ab, ae, crp, ccol, cval, cnt_out);
+        k_num_hash<SR, NT, LOG2T><<<(unsigned)nr, NT, 0, cs(P)>>>(A, B, rows, ab, ae, P->flops.as<int64_t>(), crp, ccol,
+                                                                  cval, cnt_out);
     });
 }
 
@@ -1362,7 +1363,7 @@ static spg_status merge_launch(spg_plan P, int32_t c, const LayerSet& ls, int64_
             SPG_TRY((merge_kway_launch<SR, true>(P, c, ls, ref, nr, cnt, orp, ocol, oval)));
         } else if (bb == MBIN_SORT) {
             SPG_TRY(launch(P, "merge_sort", [&] {
-                k_merge_sort<SR, true><<<grid_for(nr, 4), 256, 0, cs(P)>>>(c, ls, ref, cnt, orp, ocol, oval);
+                k_merge_sort<SR><<<grid_for(nr, 4), 256, 0, cs(P)>>>(c, ls, ref, orp, ocol, oval);
             }));
         } else if (bb == MBIN_SMALL) {
             SPG_TRY(launch(P, "merge_small", [&] {
@@ -1430,15 +1431,15 @@ static LayerSet layer_set(int32_t nlayers, const spg_csr* layers) {
 
 // Row analysis of the merge: total lengths, bins, per-bin lists; then the
 // bin counts are read back (synchronizing) into counts[MBINS].
-static spg_status merge_classify(spg_plan P, int32_t c, const LayerSet& ls, int64_t m, int64_t* tl, uint8_t* mbin,
+static spg_status merge_classify(spg_plan P, int32_t c, const LayerSet& ls, int64_t m, int64_t n, int64_t* tl, uint8_t* mbin,
                                  int32_t* mlists, int64_t* mstats, int32_t* mctr, int64_t* counts,
                                  int64_t* host_buf) {
     SPG_TRY(fill_i64(P, mstats, 2 * NBINS, 0));
     SPG_TRY(fill_i32(P, mctr, NBINS, 0));
     if (m > 0) {
         SPG_TRY(launch(P, "merge_rowinfo", [&] {
-            k_merge_rowinfo<<<(unsigned)std::min<int64_t>(grid_for(m, 256), 1024), 256, 0, cs(P)>>>(m, c, ls, tl, mbin,
-                                                                                                 mstats);
+            k_merge_rowinfo<<<(unsigned)std::min<int64_t>(grid_for(m, 256), 1024), 256, 0, cs(P)>>>(
+                m, c, ls, n <= MS_SPAN_MAX ? 1 : 0, tl, mbin, mstats);
         }));
         SPG_TRY(launch(P, "bin_scatter", [&] {
             k_bin_scatter<<<grid_for(m, CLASS_NT), CLASS_NT, 0, cs(P)>>>(
@@ -1475,7 +1476,7 @@ extern "C" spg_status spgemm_merge_layers(spg_plan P, spg_semiring sr, int32_t n
         SPG_TRY(P->mlists.ensure(4 * mm, "merge lists"));
         SPG_TRY(P->mstats.ensure(sizeof(int64_t) * 4 * NBINS, "merge stats"));
         SPG_TRY(P->mctr.ensure(sizeof(int32_t) * 64, "merge counters"));
-        SPG_TRY(merge_classify(P, nlayers, ls, m, P->merge_len.as<int64_t>(), P->mbin.as<uint8_t>(),
+        SPG_TRY(merge_classify(P, nlayers, ls, m, n, P->merge_len.as<int64_t>(), P->mbin.as<uint8_t>(),
                                P->mlists.as<int32_t>(), P->mstats.as<int64_t>(), P->mctr.as<int32_t>(), P->merge_counts,
                                P->h_stats));
         P->merge_sig = desc;
@@ -1595,7 +1596,7 @@ extern "C" spg_status spgemm_merge_layers_noalloc(void* stream, spg_semiring sr,
     const LayerSet ls = layer_set(nlayers, layers);
     int64_t counts[2 * NBINS] = {};
     // each pass classifies the rows itself, so no state is kept between calls
-    SPG_TRY(merge_classify(&T, nlayers, ls, m, L.tl, L.mbin, L.mlists, L.mstats, L.mctr, counts, host_buf));
+    SPG_TRY(merge_classify(&T, nlayers, ls, m, layers[0].ncols, L.tl, L.mbin, L.mlists, L.mstats, L.mctr, counts, host_buf));
     if (count_pass) {
         int64_t* cnt = out_row_ptr + 1;
         SPG_TRY(fill_i64(&T, cnt, m, 0));

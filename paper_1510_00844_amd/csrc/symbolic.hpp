@@ -250,6 +250,7 @@ constexpr int SW_SLOTS = 1 << SW_LOG2;
 __global__ void __launch_bounds__(256) k_sym_hash_wave(Csr A, Csr B, BinRef ref, const int64_t* a_beg,
                                                        const int64_t* a_end, int64_t* cnt) {
     __shared__ int4 tab4[4][SW_SLOTS / 4];
+    __shared__ __align__(4) uint8_t marks[4][4 * SPG_WAVE];
     int4* T4 = tab4[threadIdx.x >> 6];
     int32_t* T = reinterpret_cast<int32_t*>(T4);
     const int lane = lane_id();
@@ -262,7 +263,7 @@ __global__ void __launch_bounds__(256) k_sym_hash_wave(Csr A, Csr B, BinRef ref,
         wave_lds_sync();
         int32_t mine = 0;
         wave_products<4, int32_t>(
-            a_beg[i], a_end[i],
+            a_beg[i], a_end[i], marks[threadIdx.x >> 6],
             [&](int64_t p, int64_t& bs, int32_t& len, int32_t&) {
                 const int64_t k = A.col[p];
                 bs = B.rp[k];

@@ -12,6 +12,7 @@ import torch
 
 import oracle
 import paper_1510_00844_amd as spg
+import synth
 from gpu_util import check_full_vs_oracle, to_dev
 from synth.gen import canonical_from_coo
 
@@ -135,4 +136,85 @@ def test_row_analysis_lengths(window, reps):
     assert sum(st["num_flops"]) == flops.sum() and sum(st["num_cnnz"]) == C.nnz
     inside = (A.col >= (lo or 0)) & (A.col < (k if hi is None else hi))
     assert sum(st["sym_annz"]) == sum(st["num_annz"]) == int(inside.sum())
+    plan.close()
+
+
+@pytest.mark.parametrize("spread", ["wide", "clustered", "doubled"])
+@pytest.mark.parametrize("sr", ["f64", "i64", "bool"])
+def test_sorted_product_rows(spread, sr):
+    """Rows of the one-wave bins: product counts around the steps of 64 and
+    the 128, 256 and 512 that a bin's rows may sort, more than 64 A entries,
+    clustered columns (a bucket of more than 16) and runs of equal columns
+    across steps; FP64 adds in ascending k and equals the oracle bit for bit."""
+    rng = np.random.default_rng(5)
+    K, n = 400, 30000
+    blen = np.concatenate([rng.integers(0, 4, 300), rng.integers(4, 70, 100)])
+    if spread == "wide":
+        cols = [rng.choice(n, c, replace=False) for c in blen]
+    elif spread == "clustered":
+        cols = [np.concatenate([[0], 20000 + rng.choice(400, c - 1, replace=False)]) if c else [] for c in blen]
+    else:
+        cols = [7 * rng.choice(90, c, replace=False) for c in blen]
+    br = np.repeat(np.arange(K), blen)
+    B = canonical_from_coo(K, n, br, np.concatenate(cols).astype(np.int64), rng.uniform(-1, 1, br.size), dup="first")
+    rows, acols = [], []
+    targets = [65, 66, 127, 128, 129, 191, 192, 193, 255, 256, 257, 300, 383, 384, 385, 500, 511, 512, 513, 600]
+    r = 0
+    for t in targets * 3:
+        ks, f = [], 0
+        pool = rng.permutation(300 if r % 3 == 0 else K)  # every third row: short B rows, many A entries
+        for k in pool:
+            if blen[k] and f + blen[k] <= t:
+                ks.append(k)
+                f += blen[k]
+        ks += [k for k in pool if blen[k] == 0][:5]
+        rows += [r] * len(ks)
+        acols += ks
+        r += 1
+    A = canonical_from_coo(r, K, np.array(rows), np.array(acols), rng.uniform(-1, 1, len(rows)), dup="first")
+    if sr != "f64":
+        kind = {"i64": "ones_i64", "bool": "true_bool"}[sr]
+        A, B = synth.with_values(A, kind), synth.with_values(B, kind)
+    # (no bitmap rows: n / 32 products and fewer)
+    plan = spg.Plan()
+    C = spg.spgemm(plan, sr, to_dev(A, sr), to_dev(B, sr))
+    check_full_vs_oracle(C, A, B, sr)
+    if sr == "f64":
+        ref = oracle.spgemm(A, B, sr)
+        flops = oracle.row_flops(A, B)
+        cnt = np.diff(ref.row_ptr)
+        # the rows a one-wave bin sorts: as many products as its steps hold, four per output
+        slots = np.select([cnt <= 96, cnt <= 192, cnt <= 384], [256, 256, 512], 0)
+        pick = np.repeat((flops <= slots) & (flops <= 4 * cnt), cnt)
+        assert pick.any() and np.array_equal(C.val.cpu().numpy()[pick], ref.val[pick])
+    plan.close()
+
+
+@pytest.mark.parametrize("layers", [2, 3, 4, 5, 8, 9, 16, 64])
+@pytest.mark.parametrize("sr", ["f64", "i64", "bool"])
+def test_merge_row_lengths(layers, sr):
+    """Merge rows at the edges of their bins (64, 128, 384, 512 entries), empty
+    layers first, last and in between, against the oracle bit for bit."""
+    rng = np.random.default_rng(layers)
+    sizes = [0, 1, 2, 63, 64, 65, 66, 127, 128, 129, 130, 255, 256, 257, 383, 384, 385, 511, 512, 513, 700]
+    n = 5000
+    parts = []
+    owner = []
+    for i, L in enumerate(sizes * 2):
+        use = rng.choice(layers, max(1, layers // (1 + i % 3)), replace=False)  # some layers empty in the row
+        owner.append(np.bincount(rng.choice(use, L), minlength=layers) if L else np.zeros(layers, int))
+    for l in range(layers):
+        lens = np.array([o[l] for o in owner])
+        width = [n if i % 2 else 900 for i in range(len(lens))]  # narrow rows: many equal columns
+        cols = [rng.choice(width[i], c, replace=False) for i, c in enumerate(lens)]
+        rows = np.repeat(np.arange(len(lens)), lens)
+        M = canonical_from_coo(len(lens), n, rows, np.concatenate(cols).astype(np.int64), rng.uniform(-1, 1, rows.size),
+                               dup="first")
+        parts.append(M if sr == "f64" else synth.with_values(M, {"i64": "ones_i64", "bool": "true_bool"}[sr]))
+    plan = spg.Plan()
+    ref = oracle.merge(parts, sr)
+    for got in (spg.spgemm_merge_layers(plan, sr, [to_dev(M, sr) for M in parts]),
+                spg.spgemm_merge_layers_noalloc(sr, [to_dev(M, sr) for M in parts])):
+        rp, col, val = got.to_numpy()
+        assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
     plan.close()
