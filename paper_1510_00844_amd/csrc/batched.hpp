@@ -32,21 +32,6 @@ __device__ inline int find_instance(const BatchDesc* d, int32_t nb, int64_t r) {
     return lo;
 }
 
-// Largest b with d[b].nz_off <= e: the instance holding batch entry e.
-__device__ inline int find_instance_nz(const BatchDesc* d, int32_t nb, int64_t e) {
-    int lo = 0, hi = nb;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (d[mid].nz_off <= e) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-// Grid-stride over x < max(rows + 1, nnz): row pointer x (shifted by the
-// entries before its instance) and entry x (column shifted by the columns
-// before its instance, value copied), so reads and writes are coalesced.
-// The instances' first rows and entries are staged in LDS for the searches.
-// vw = value bytes (8 or 1; 0 = no values).
 constexpr int BATCH_LDS_MAX = 1024;  // instances whose offsets fit the LDS tables
 
 __device__ inline int find_sorted(const int64_t* off, int32_t nb, int64_t x) {
@@ -58,9 +43,70 @@ __device__ inline int find_sorted(const int64_t* off, int32_t nb, int64_t x) {
     return lo;
 }
 
+// The batch's row pointers (shifted by the entries before the row's instance)
+// and entries (columns shifted by the columns before it, values copied).  vw =
+// value bytes (8 or 1; 0 = no values); structure = 0: the row pointers and
+// columns are in place from an earlier call with the same instances and only
+// the values are copied.
+//
+// Bound by memory, so the entries are taken BATCH_TILE at a time with the loads
+// of a thread in flight together: one search per tile, and where the tile lies
+// in one instance (nearly always) one base address for all of it.  Three
+// operands of 64 grids of 16^3 ... 64^3 points, values only: 275 us with a
+// search and one load at a time per thread, 155 so.
+constexpr int BATCH_U = 8;
+constexpr int BATCH_TILE = 256 * BATCH_U;
+
+template <typename V>
+__device__ inline void assemble_entries(const BatchDesc* d, int32_t nb, const int64_t* s_nz, bool lds, int64_t base,
+                                        int64_t nnz, bool structure, int32_t* col, V* val) {
+    auto first = [&](int b) { return lds ? s_nz[b] : d[b].nz_off; };
+    int b = 0;  // the tile's first entry: the same address for every thread
+    if (lds) {
+        b = find_sorted(s_nz, nb, base);
+    } else {
+        for (int lo = 0, hi = nb; hi - lo > 1; b = lo) {
+            const int mid = (lo + hi) >> 1;
+            if (d[mid].nz_off <= base) lo = mid; else hi = mid;
+        }
+    }
+    const int64_t tile_end = base + BATCH_TILE < nnz ? base + BATCH_TILE : nnz;
+    int64_t x[BATCH_U];
+    V v[BATCH_U];
+    int32_t c[BATCH_U];
+    if (tile_end - base == BATCH_TILE && (b + 1 == nb || first(b + 1) >= tile_end)) {
+        const BatchDesc& D = d[b];
+        const int64_t e = base - D.nz_off + D.rp[0] + threadIdx.x;
+        const V* sv = (const V*)D.val;
+#pragma unroll
+        for (int u = 0; u < BATCH_U; ++u) {
+            if (structure) c[u] = D.col[e + u * 256];
+            if (val) v[u] = sv ? sv[e + u * 256] : V(1);
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH_U; ++u) {
+            x[u] = base + u * 256 + threadIdx.x;
+            if (structure) col[x[u]] = (int32_t)(c[u] + D.col_off);
+            if (val) val[x[u]] = v[u];
+        }
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < BATCH_U; ++u) {
+        x[u] = base + u * 256 + threadIdx.x;
+        if (x[u] >= tile_end) break;
+        while (b + 1 < nb && first(b + 1) <= x[u]) ++b;
+        const BatchDesc& D = d[b];
+        const int64_t e = x[u] - D.nz_off + D.rp[0];
+        if (structure) col[x[u]] = (int32_t)(D.col[e] + D.col_off);
+        if (val) val[x[u]] = D.val ? ((const V*)D.val)[e] : V(1);
+    }
+}
+
 __global__ void __launch_bounds__(256) k_batch_assemble(const BatchDesc* d, int32_t nb, int64_t rows, int64_t nnz,
                                                         int32_t vw, int32_t structure, int64_t* rp, int32_t* col,
                                                         void* val) {
+    // the instances' first entries and rows, staged for the searches
     __shared__ int64_t s_row[BATCH_LDS_MAX], s_nz[BATCH_LDS_MAX];
     const bool lds = nb <= BATCH_LDS_MAX;
     if (lds)
@@ -69,30 +115,18 @@ __global__ void __launch_bounds__(256) k_batch_assemble(const BatchDesc* d, int3
             s_nz[b] = d[b].nz_off;
         }
     __syncthreads();
-    // structure = 0: the row pointers and columns are in place from an
-    // earlier call with the same instances; only the values are copied
-    const int64_t n = structure ? (rows + 1 > nnz ? rows + 1 : nnz) : nnz;
-    for (int64_t base = (int64_t)blockIdx.x * 256; base < n; base += (int64_t)gridDim.x * 256) {
-        const int64_t x = base + threadIdx.x;
-        if (structure && x < rows) {
-            const BatchDesc& D = d[lds ? find_sorted(s_row, nb, x) : find_instance(d, nb, x)];
-            rp[x] = D.nz_off + (D.rp[x - D.row_off] - D.rp[0]);
-        } else if (structure && x == rows) {
-            rp[rows] = nnz;
-        }
-        if (base < nnz) {
-            // the instance of the block's first entry (one search, the same
-            // address for every thread), then forward to this thread's entry
-            int b = lds ? find_sorted(s_nz, nb, base) : find_instance_nz(d, nb, base);
-            while (b + 1 < nb && (lds ? s_nz[b + 1] : d[b + 1].nz_off) <= x) ++b;
-            if (x < nnz) {
-                const BatchDesc& D = d[b];
-                const int64_t e = x - D.nz_off + D.rp[0];
-                if (structure) col[x] = (int32_t)(D.col[e] + D.col_off);
-                if (vw == 8) ((uint64_t*)val)[x] = ((const uint64_t*)D.val)[e];
-                else if (vw == 1) ((uint8_t*)val)[x] = D.val ? ((const uint8_t*)D.val)[e] : (uint8_t)1;
+    if (structure)
+        for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x <= rows; x += (int64_t)gridDim.x * 256) {
+            if (x == rows) {
+                rp[rows] = nnz;
+            } else {
+                const BatchDesc& D = d[lds ? find_sorted(s_row, nb, x) : find_instance(d, nb, x)];
+                rp[x] = D.nz_off + (D.rp[x - D.row_off] - D.rp[0]);
             }
         }
+    for (int64_t base = (int64_t)blockIdx.x * BATCH_TILE; base < nnz; base += (int64_t)gridDim.x * BATCH_TILE) {
+        if (vw == 8) assemble_entries<uint64_t>(d, nb, s_nz, lds, base, nnz, structure, col, (uint64_t*)val);
+        else assemble_entries<uint8_t>(d, nb, s_nz, lds, base, nnz, structure, col, vw == 1 ? (uint8_t*)val : nullptr);
     }
 }
 

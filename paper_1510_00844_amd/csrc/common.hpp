@@ -374,22 +374,59 @@ __device__ inline uint64_t wave_bitonic_sort_u64(uint64_t key) {
     return key;
 }
 
-// The same sort for 32-bit keys: one lane exchange, a min and a max per
-// step instead of two exchanges and 64-bit selects.
-__device__ inline uint32_t wave_bitonic_sort_u32(uint32_t key) {
+// The same sort for R rows of 32-bit keys at once: one lane exchange, a min and
+// a max per step instead of two exchanges and 64-bit selects, the rows' steps
+// interleaved so that one's exchange hides the other's.  Unused lanes hold the
+// largest key; the rows have at most n keys (wave-uniform), so the stages
+// beyond the first power of two >= n would move nothing and are left out.
+template <int R>
+__device__ inline void wave_bitonic_sort_u32(uint32_t (&key)[R], int n) {
     const int lane = lane_id();
 #pragma unroll
     for (int k = 2; k <= SPG_WAVE; k <<= 1) {
+        if (k > 2 && n <= k / 2) break;
 #pragma unroll
         for (int j = k >> 1; j > 0; j >>= 1) {
-            const uint32_t o = lane_xor_u32(key, j);
             const bool keep_min = ((lane & j) == 0) == ((lane & k) == 0);
-            const uint32_t mn = key < o ? key : o;
-            const uint32_t mx = key < o ? o : key;
-            key = keep_min ? mn : mx;
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const uint32_t o = lane_xor_u32(key[u], j);
+                const uint32_t mn = key[u] < o ? key[u] : o;
+                const uint32_t mx = key[u] < o ? o : key[u];
+                key[u] = keep_min ? mn : mx;
+            }
         }
     }
-    return key;
+}
+__device__ inline uint32_t wave_bitonic_sort_u32(uint32_t key, int n) {
+    uint32_t k[1] = {key};
+    wave_bitonic_sort_u32(k, n);
+    return k[0];
+}
+
+// One row's n <= 64 entries, ordered by (column, position): lane l < n holds
+// entry l's column and value.  Returns the mask of the lanes that begin a run
+// of equal columns and leaves in v of those lanes the run's values added left
+// to right.  Which lanes still add is a mask shifted once a step, computed
+// once for the wave, so a step is a lane shift and an add.
+template <int SR>
+__device__ inline uint64_t wave_fold_sorted(uint32_t col, typename Sr<SR>::acc_t& v, int n) {
+    typedef Sr<SR> S;
+    typedef typename S::acc_t V;
+    const uint32_t prev = lane_prev(col);
+    const uint64_t all = n < SPG_WAVE ? (1ull << n) - 1 : ~0ull;
+    const uint64_t heads = (__builtin_amdgcn_ballot_w64(prev != col) | 1ull) & all;
+    uint64_t more = (all & ~heads) >> 1;  // lane l: entry l + s continues a run
+    uint64_t open = heads & more;         // heads whose run reaches s entries further
+    V nv = v;
+    while (open) {
+        nv = lane_next(nv);
+        const V sum = S::add(v, nv);
+        v = __builtin_amdgcn_inverse_ballot_w64(open) ? sum : v;
+        more >>= 1;
+        open &= more;
+    }
+    return heads;
 }
 
 __device__ inline uint32_t hash_slot(int32_t key, int log2t) {

@@ -346,7 +346,8 @@ __global__ void __launch_bounds__(256) k_merge_small(int32_t c, LayerSet layers_
     const int32_t* rows;
     int64_t nrows;
     ref.locate(rows, nrows);
-    for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < nrows; r += (int64_t)gridDim.x * 4) {
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int64_t r = (int64_t)blockIdx.x * 4 + wv; r < nrows; r += (int64_t)gridDim.x * 4) {
     const int64_t i = rows[r];
     const int lane = lane_id();
     int pos = 0, my_l = -1;
@@ -367,33 +368,17 @@ __global__ void __launch_bounds__(256) k_merge_small(int32_t c, LayerSet layers_
         if (!cnt) v = S::load(layers[my_l].val, my_q);
     }
     key = wave_bitonic_sort_u64(key);
-    const bool valid = key != ~0ull;
-    const uint64_t col = key >> 6;
-    const uint64_t prev = lane_prev(col);
-    const bool head = valid && (lane == 0 || prev != col);
-    const uint64_t heads = __ballot(head);
+    const uint32_t col = (uint32_t)(key >> 6);
+    v = __shfl(v, (int)(key & 63), SPG_WAVE);
+    const uint64_t heads = wave_fold_sorted<SR>(col, v, pos);
     if (cnt) {
         if (lane == 0) cnt[i] = __popcll(heads);
         continue;
     }
-    v = __shfl(v, (int)(key & 63), SPG_WAVE);
-    V acc = v;
-    bool open = head;
-    uint64_t ncol = col;
-    V nv = v;
-    int nvalid = valid ? 1 : 0;
-    for (int s = 1; s < SPG_WAVE; ++s) {  // entry s lanes above, one lane per step
-        if (!__any(open)) break;
-        ncol = lane_next(ncol);
-        nv = lane_next(nv);
-        nvalid = lane_next(nvalid);
-        open = open && (lane + s < SPG_WAVE) && nvalid != 0 && ncol == col;
-        if (open) acc = S::add(acc, nv);
-    }
-    if (head) {
+    if ((heads >> lane) & 1) {
         const int64_t o = out_rp[i] + lanes_below(heads);
         out_col[o] = (int32_t)col;
-        if (out_val) S::store(out_val, o, acc);
+        if (out_val) S::store(out_val, o, v);
     }
     }
 }

@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(256) k_sort_row_cols(int64_t nrows, const int6
     const int64_t len = rp[r + 1] - s;
     if (len > SPG_WAVE) return;
     const int lane = lane_id();
-    const uint32_t k = wave_bitonic_sort_u32(lane < len ? (uint32_t)col[s + lane] : 0xffffffffu);
+    const uint32_t k = wave_bitonic_sort_u32(lane < len ? (uint32_t)col[s + lane] : 0xffffffffu, (int)len);
     if (lane < len) col[s + lane] = (int32_t)k;
 }
 

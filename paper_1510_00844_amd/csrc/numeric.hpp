@@ -87,7 +87,17 @@ __global__ void __launch_bounds__(256) k_num_tiny(Csr A, Csr B, const int32_t* r
 }
 
 // cnt_out (optional) receives each row's output count.  4 waves per block,
-// SMALL_ROWS rows per wave (their loads in flight together).
+// SMALL_ROWS rows per wave (their loads in flight together; four rows measured
+// 2 to 3 % slower than two).
+//
+// It was bound by instruction issue (81 % of the vector slots): a search of six
+// lane exchanges for each product's segment, 64-bit addresses of the windows per
+// lane, one row's sort after another's, and a fold that shifted columns, values
+// and validity and compared them at every step.  Now the segments are marked,
+// the wave's rows are scalars, the sorts run side by side and end at the row's
+// size, and a fold step is a shift and an add: 350 -> 170 vector instructions a
+// row; the two products of 64 grids of 16^3 ... 64^3 points 700 -> 530 us, at 3.5
+// TB/s past L2, bound by latency at full occupancy.
 template <int SR>
 __global__ void __launch_bounds__(256) k_num_small(Csr A, Csr B, const int32_t* rows, int32_t nrows,
                                                    const int64_t* a_beg, const int64_t* a_end,
@@ -95,61 +105,61 @@ __global__ void __launch_bounds__(256) k_num_small(Csr A, Csr B, const int32_t* 
                                                    int64_t* cnt_out) {
     typedef Sr<SR> S;
     typedef typename S::acc_t V;
-    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    // the wave's number as a scalar: its rows' windows are then scalar loads
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t w = (int64_t)blockIdx.x * 4 + wv;
     if (w * SMALL_ROWS >= nrows) return;  // whole wave leaves; no block barriers below
     const int lane = lane_id();
+    __shared__ uint8_t s_mark[4][SMALL_ROWS * SPG_WAVE];
     V vals[SMALL_ROWS];
-    uint64_t keys[SMALL_ROWS];
+    uint32_t key[SMALL_ROWS];  // columns, then (32-bit sort) columns and product order
     int64_t row[SMALL_ROWS];
-    for_small_rows(A, B, rows, nrows, w, a_beg, a_end, [&](int u, int64_t i, bool have, int64_t p, int64_t q) {
+    int n[SMALL_ROWS];
+    for_small_rows(A, B, rows, nrows, w, a_beg, a_end, s_mark[wv], n,
+                   [&](int u, int64_t i, bool have, int64_t p, int64_t q) {
         row[u] = i;
         vals[u] = S::zero();
-        keys[u] = ~0ull;
+        key[u] = ~0u;
         if (have) {
             vals[u] = S::mul(S::load(A.val, p), S::load(B.val, q));
-            keys[u] = ((uint64_t)(uint32_t)B.col[q] << 6) | (uint64_t)lane;  // (column, product order)
+            key[u] = (uint32_t)B.col[q];
         }
     });
+    int order[SMALL_ROWS];  // the product this lane takes after the sort
+    // (column, lane) fits 32 bits below 2^26 - 1 columns (the all-ones key stays
+    // the empty lane's): the cheaper 32-bit sort of all rows together
+    if (B.ncols < (1ll << 26) - 1) {
+        int most = 0;
+#pragma unroll
+        for (int u = 0; u < SMALL_ROWS; ++u) {
+            key[u] = lane < n[u] ? key[u] << 6 | (uint32_t)lane : ~0u;
+            most = n[u] > most ? n[u] : most;
+        }
+        wave_bitonic_sort_u32(key, most);
+#pragma unroll
+        for (int u = 0; u < SMALL_ROWS; ++u) {
+            order[u] = (int)(key[u] & 63);
+            key[u] >>= 6;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < SMALL_ROWS; ++u) {
+            const uint64_t k = wave_bitonic_sort_u64(lane < n[u] ? (uint64_t)key[u] << 6 | (uint64_t)lane : ~0ull);
+            order[u] = (int)(k & 63);
+            key[u] = (uint32_t)(k >> 6);
+        }
+    }
 #pragma unroll
     for (int u = 0; u < SMALL_ROWS; ++u) {
         if (w * SMALL_ROWS + u >= nrows) break;
-        const int64_t i = row[u];
-        // (column, lane) fits 32 bits below 2^26 - 1 columns (the all-ones
-        // key stays the empty lane's): the cheaper 32-bit sort
-        uint64_t key;
-        if (B.ncols < (1ll << 26) - 1) {
-            const uint32_t k32 = wave_bitonic_sort_u32((uint32_t)keys[u]);
-            key = k32 == 0xffffffffu ? ~0ull : (uint64_t)k32;
-        } else {
-            key = wave_bitonic_sort_u64(keys[u]);
+        V v = __shfl(vals[u], order[u], SPG_WAVE);  // value travels with its key
+        const uint64_t heads = wave_fold_sorted<SR>(key[u], v, n[u]);
+        if (__builtin_amdgcn_inverse_ballot_w64(heads)) {
+            const int64_t o = c_rp.off(row[u]) + lanes_below(heads);
+            c_col[o] = (int32_t)key[u];
+            if (c_val) S::store(c_val, o, v);
         }
-        const bool valid = key != ~0ull;
-        const V v = __shfl(vals[u], (int)(key & 63), SPG_WAVE);  // value travels with its key
-        const uint64_t col = key >> 6;
-        const uint64_t prev = lane_prev(col);
-        const bool head = valid && (lane == 0 || prev != col);
-        // fold the run that starts at each head, left to right: at step s
-        // every lane holds the entry s lanes above it (shifted one lane per step)
-        V acc = v;
-        bool open = head;
-        uint64_t ncol = col;
-        V nv = v;
-        int nvalid = valid ? 1 : 0;
-        for (int s = 1; s < SPG_WAVE; ++s) {
-            if (!__any(open)) break;
-            ncol = lane_next(ncol);
-            nv = lane_next(nv);
-            nvalid = lane_next(nvalid);
-            open = open && (lane + s < SPG_WAVE) && nvalid != 0 && ncol == col;
-            if (open) acc = S::add(acc, nv);
-        }
-        const uint64_t heads = __ballot(head);
-        if (head) {
-            const int64_t o = c_rp.off(i) + lanes_below(heads);
-            c_col[o] = (int32_t)col;
-            if (c_val) S::store(c_val, o, acc);
-        }
-        if (cnt_out && lane == 0) cnt_out[i] = __popcll(heads);
+        if (cnt_out && lane == 0) cnt_out[row[u]] = __popcll(heads);
     }
 }
 

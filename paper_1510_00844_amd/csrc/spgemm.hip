@@ -2306,7 +2306,7 @@ static bool same_csr(const spg_csr& x, const spg_csr& y) {
 }
 
 static unsigned assemble_grid(int64_t rows, int64_t nnz) {
-    return (unsigned)std::min<int64_t>(grid_for(std::max(rows + 1, nnz), 256), 8192);
+    return (unsigned)std::min<int64_t>(grid_for(std::max((rows + 1) * BATCH_U, nnz), BATCH_TILE), 8192);
 }
 
 // The whole device sequence of one batched call.  eager: may allocate and

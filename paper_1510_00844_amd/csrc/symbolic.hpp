@@ -64,19 +64,23 @@ __device__ inline bool wave_locate_product(const Csr& A, const Csr& B, int64_t b
 // The same for SMALL_ROWS rows at once whose A windows hold at most 64
 // entries (one group): each dependent load level (A columns, B extents, B
 // entries) is issued for all rows before any is waited for, so a wave keeps
-// that many rows' loads in flight.  Lane f takes product f of row u.
+// that many rows' loads in flight.  Lane f takes product f of row u: the lane
+// of every non-empty B segment is marked in LDS (64 bytes a row, the wave's
+// own) at its first product, and a running maximum of the marks gives each
+// product its segment.  n[u] = the row's products.
 constexpr int SMALL_ROWS = 2;
 __device__ inline void wave_locate_rows(const Csr& A, const Csr& B, const int64_t* beg, const int64_t* end,
-                                        bool* have, int64_t* p_out, int64_t* q_out) {
+                                        uint8_t* marks, int* n, int64_t* p_out, int64_t* q_out) {
     const int lane = lane_id();
     int64_t kk[SMALL_ROWS];
 #pragma unroll
     for (int u = 0; u < SMALL_ROWS; ++u) {
         const int64_t p = beg[u] + lane;
         kk[u] = p < end[u] ? (int64_t)A.col[p] : -1;
+        marks[u * SPG_WAVE + lane] = 0;
     }
     int64_t bs[SMALL_ROWS];
-    int len[SMALL_ROWS];
+    int len[SMALL_ROWS], off[SMALL_ROWS];
 #pragma unroll
     for (int u = 0; u < SMALL_ROWS; ++u) {
         bs[u] = 0;
@@ -86,32 +90,31 @@ __device__ inline void wave_locate_rows(const Csr& A, const Csr& B, const int64_
             len[u] = (int)(B.rp[kk[u] + 1] - bs[u]);
         }
     }
+    wave_lds_sync();
 #pragma unroll
     for (int u = 0; u < SMALL_ROWS; ++u) {
         const int incl = wave_inclusive_scan_add(len[u]);
-        const int total = __builtin_amdgcn_readlane(incl, SPG_WAVE - 1);
-        int t = 0;  // first lane whose inclusive count exceeds this lane's product
-#pragma unroll
-        for (int step = SPG_WAVE / 2; step > 0; step >>= 1) {
-            const int v = __shfl(incl, t + step - 1, SPG_WAVE);
-            if (v <= lane) t += step;
-        }
-        t = t < SPG_WAVE ? t : SPG_WAVE - 1;
-        const int64_t bst = __shfl(bs[u], t, SPG_WAVE);
-        const int excl = __shfl(incl - len[u], t, SPG_WAVE);
-        have[u] = lane < total;
-        p_out[u] = beg[u] + t;
-        q_out[u] = bst + (lane - excl);
+        n[u] = __builtin_amdgcn_readlane(incl, SPG_WAVE - 1);  // at most 64
+        off[u] = incl - len[u];
+        if (len[u] > 0 && off[u] < SPG_WAVE) marks[u * SPG_WAVE + off[u]] = (uint8_t)lane;
     }
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < SMALL_ROWS; ++u) {
+        const int t = wave_inclusive_scan_max(marks[u * SPG_WAVE + lane]);
+        p_out[u] = beg[u] + t;
+        q_out[u] = lane_get(bs[u] - off[u], t) + lane;
+    }
+    wave_lds_sync();  // read before the next rows clear them
 }
 
 // The rows of one wave: SMALL_ROWS consecutive list entries.  locate(u, i,
-// have, p, q) gets each row's products; rows past the list are skipped, and a
-// row with more than 64 A entries in the window (empty B rows among them)
-// falls back to the one-row search.
+// have, p, q) gets each row's products (n[u] of them); rows past the list are
+// skipped (n[u] = 0), and a row with more than 64 A entries in the window
+// (empty B rows among them) falls back to the one-row search.
 template <class Body>
 __device__ inline void for_small_rows(const Csr& A, const Csr& B, const int32_t* rows, int64_t nrows, int64_t w,
-                                      const int64_t* a_beg, const int64_t* a_end, Body body) {
+                                      const int64_t* a_beg, const int64_t* a_end, uint8_t* marks, int* n, Body body) {
     int64_t i[SMALL_ROWS], beg[SMALL_ROWS], end[SMALL_ROWS];
     bool ok[SMALL_ROWS];
 #pragma unroll
@@ -127,20 +130,19 @@ __device__ inline void for_small_rows(const Csr& A, const Csr& B, const int32_t*
         end[u] = ok[u] ? a_end[i[u]] : 0;
         one_group = one_group && end[u] - beg[u] <= SPG_WAVE;
     }
-    bool have[SMALL_ROWS];
+    const int lane = lane_id();
     int64_t p[SMALL_ROWS], q[SMALL_ROWS];
     if (one_group) {
-        wave_locate_rows(A, B, beg, end, have, p, q);
+        wave_locate_rows(A, B, beg, end, marks, n, p, q);
     } else {
 #pragma unroll
         for (int u = 0; u < SMALL_ROWS; ++u) {
             p[u] = q[u] = 0;
-            have[u] = wave_locate_product(A, B, beg[u], end[u], p[u], q[u]);
+            n[u] = __popcll(__ballot(wave_locate_product(A, B, beg[u], end[u], p[u], q[u])));
         }
     }
 #pragma unroll
-    for (int u = 0; u < SMALL_ROWS; ++u)
-        if (ok[u]) body(u, i[u], have[u], p[u], q[u]);
+    for (int u = 0; u < SMALL_ROWS; ++u) body(u, i[u], lane < n[u], p[u], q[u]);
 }
 
 // 4 waves per block, SMALL_ROWS rows per wave, the waves striding over the
@@ -154,11 +156,12 @@ static_assert(SS_SLOTS >= 2 * SPG_WAVE && SS_SLOTS % SPG_WAVE == 0, "a set holds
 __global__ void __launch_bounds__(256) k_sym_small(Csr A, Csr B, BinRef ref, const int64_t* a_beg,
                                                    const int64_t* a_end, int64_t* cnt) {
     __shared__ int32_t sets[4][SMALL_ROWS][SS_SLOTS];
+    __shared__ uint8_t s_mark[4][SMALL_ROWS * SPG_WAVE];
     const int32_t* rows;
     int64_t nrows;
     ref.locate(rows, nrows);
     const int lane = lane_id();
-    const int wv = (int)(threadIdx.x >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (int64_t w = (int64_t)blockIdx.x * 4 + wv; w * SMALL_ROWS < nrows; w += (int64_t)gridDim.x * 4) {
 #pragma unroll
         for (int u = 0; u < SMALL_ROWS; ++u)
@@ -166,7 +169,9 @@ __global__ void __launch_bounds__(256) k_sym_small(Csr A, Csr B, BinRef ref, con
         wave_lds_sync();
         int32_t mine[SMALL_ROWS];
         int64_t row[SMALL_ROWS];
-        for_small_rows(A, B, rows, nrows, w, a_beg, a_end, [&](int u, int64_t i, bool have, int64_t, int64_t q) {
+        int n[SMALL_ROWS];
+        for_small_rows(A, B, rows, nrows, w, a_beg, a_end, s_mark[wv], n,
+                       [&](int u, int64_t i, bool have, int64_t, int64_t q) {
             row[u] = i;
             mine[u] = 0;
             if (have) {

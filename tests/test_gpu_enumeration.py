@@ -218,3 +218,79 @@ def test_merge_row_lengths(layers, sr):
         rp, col, val = got.to_numpy()
         assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col) and np.array_equal(val, ref.val)
     plan.close()
+
+
+@pytest.mark.parametrize("n", [60, 30000, (1 << 26) - 2, (1 << 26) + 5])
+@pytest.mark.parametrize("sr", ["f64", "i64", "bool"])
+def test_small_product_rows(n, sr):
+    """Rows of up to 64 products: every count around the stages of the sort
+    (2, 4 ... 64), B segments of 0, 1 and more, more than 64 A entries of empty B
+    rows, runs of equal columns up to the whole row, odd numbers of rows, and
+    columns on both sides of the 32-bit sort's limit.  FP64 adds in ascending k and
+    equals the oracle bit for bit."""
+    rng = np.random.default_rng(9)
+    K = 700
+    blen = np.concatenate([np.zeros(200, np.int64), np.ones(300, np.int64), rng.integers(2, 9, 150), rng.integers(9, 33, 50)])
+    span = min(n, 60)
+    cols = [np.concatenate([rng.choice(span, c - c // 2, replace=False), n - 1 - rng.choice(min(n // 2, 9000), c // 2, replace=False)])
+            if n > 60 else rng.choice(n, c, replace=False) for c in blen]
+    cols[200:260] = [np.array([n - 1])] * 60  # one column: runs as long as the row
+    br = np.repeat(np.arange(K), blen)
+    B = canonical_from_coo(K, n, br, np.concatenate(cols).astype(np.int64), rng.uniform(-1, 1, br.size), dup="first")
+    rows, acols, r = [], [], 0
+    for t in [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 47, 60, 63, 64] * 3 + [64]:
+        ks, f = [], 0
+        pool = 200 + rng.permutation({0: 60, 1: 300, 2: 500}[r % 3])
+        for k in pool:
+            if f + blen[k] <= t:
+                ks.append(k)
+                f += blen[k]
+        ks += list(rng.permutation(200)[:(0, 3, 120)[r // 2 % 3]])
+        rows += [r] * len(ks)
+        acols += ks
+        r += 1
+    A = canonical_from_coo(r, K, np.array(rows), np.array(acols), rng.uniform(-1, 1, len(rows)), dup="first")
+    if sr != "f64":
+        kind = {"i64": "ones_i64", "bool": "true_bool"}[sr]
+        A, B = synth.with_values(A, kind), synth.with_values(B, kind)
+    plan = spg.Plan()
+    for lo, hi in [(None, None), (150, 420)]:
+        C = spg.spgemm(plan, sr, to_dev(A, sr), to_dev(B, sr), lo, hi)
+        check_full_vs_oracle(C, A, B, sr, lo, hi)
+        assert oracle.row_flops(A, B, lo, hi).max() <= 64
+        if sr == "f64":
+            assert np.array_equal(C.val.cpu().numpy(), oracle.spgemm(A, B, sr, lo, hi).val)
+    plan.close()
+
+
+@pytest.mark.parametrize("sizes", [[2047, 1, 2048, 0, 2049, 3, 4095, 6144, 17], [5] * 1100])
+@pytest.mark.parametrize("sr", ["f64", "i64", "bool"])
+def test_batched_instance_edges(sizes, sr):
+    """Batches whose instances begin and end at, before and after the copy's
+    tiles of 2048 entries, and more instances than its tables hold; a second
+    call with the values changed in place follows them."""
+    rng = np.random.default_rng(4)
+    dt = {"f64": np.float64, "i64": np.int64, "bool": np.uint8}[sr]
+    draw = lambda k: (np.ones(k) if sr == "bool" else rng.integers(1, 5, k)).astype(dt)
+    inst = []
+    for nnz in sizes:
+        n, m = max(5, nnz // 7), max(2, nnz // 40)
+        flat = rng.choice(n * n, nnz, replace=False)
+        A = canonical_from_coo(n, n, flat // n, flat % n, draw(nnz), dup="first")
+        agg = rng.integers(0, m, n)
+        R = canonical_from_coo(n, m, np.arange(n), agg, draw(n), dup="first")
+        RT = canonical_from_coo(m, n, agg, np.arange(n), draw(n), dup="first")
+        inst.append([RT, A, R])
+    plan = spg.Plan()
+    dev = [[to_dev(M, sr) for M in t] for t in inst]
+    for again in range(3):
+        if again:
+            for t, d in zip(inst, dev):
+                t[1].val[:] = draw(t[1].nnz)
+                d[1].val.copy_(torch.from_numpy(t[1].val))
+        got = spg.spgemm_galerkin_batched(plan, sr, *[[d[k] for d in dev] for k in range(3)]).fetch(plan)
+        for b, (C, (RT, A, R)) in enumerate(zip(got, inst)):
+            ref = oracle.spgemm(oracle.spgemm(RT, A, sr), R, sr)
+            assert np.array_equal(C.row_ptr.cpu().numpy(), ref.row_ptr) and np.array_equal(C.col.cpu().numpy(), ref.col), b
+            assert np.array_equal(C.val.cpu().numpy(), ref.val), b  # small integers: exact
+    plan.close()
