@@ -304,12 +304,11 @@ __global__ void __launch_bounds__(256, 5) k_merge_sort(int32_t c, LayerSet layer
                 const int32_t y = x < L ? x : L - 1;
                 const int32_t* cp = (const int32_t*)(intptr_t)lane_get((int64_t)(intptr_t)m.colp, l[u0 + u]);
                 const void* vp = (const void*)(intptr_t)lane_get((int64_t)(intptr_t)m.valp, l[u0 + u]);
-                // (taken by every lane: an exchange inside the test below would
-                // read lanes that the test switches off)
+                // (taken by every lane: boolean layers may have no value array, and
+                // an exchange inside that test would read lanes that it switches off)
                 const int64_t q = lane_get(m.rel, l[u0 + u]) + y;
                 col[u0 + u] = cp[y];
-                // no value array: structure-only output (booleans: all true)
-                v[u] = (vp || SR == SR_BOOL) ? S::load(vp, q) : S::zero();
+                v[u] = S::load(vp, q);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {

@@ -1401,6 +1401,11 @@ static spg_status merge_dispatch(spg_plan P, int32_t c, const LayerSet& ls, int6
 static spg_status merge_by_sr(spg_plan P, spg_semiring sr, int32_t c, const LayerSet& ls, int64_t n,
                               const int64_t* counts, const int64_t* dev_counts, const int32_t* lists, const int64_t* tl,
                               int64_t* cnt, const int64_t* orp, int32_t* ocol, void* oval) {
+    if (!cnt && !oval) {  // structure only: the layers need no values, so none are read
+        LayerSet bare = ls;
+        for (int l = 0; l < c; ++l) bare.d[l].val = nullptr;
+        return merge_dispatch<SR_BOOL>(P, c, bare, n, counts, dev_counts, lists, tl, cnt, orp, ocol, oval);
+    }
     switch (sr) {
         case SPG_SR_PLUS_TIMES_F64: return merge_dispatch<SR_F64>(P, c, ls, n, counts, dev_counts, lists, tl, cnt, orp, ocol, oval);
         case SPG_SR_PLUS_TIMES_I64: return merge_dispatch<SR_I64>(P, c, ls, n, counts, dev_counts, lists, tl, cnt, orp, ocol, oval);

@@ -1,5 +1,6 @@
 """Matrices without a value array: boolean matrices, where it means that every
-stored entry is true, beside others that hold truth values."""
+stored entry is true, beside others that hold truth values; and any matrix
+where only the structure of the result is asked for."""
 
 import numpy as np
 import pytest
@@ -60,4 +61,20 @@ def test_merge_of_boolean_layers_with_and_without_values(c, bare):
         rp, col, val = got.to_numpy()
         assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
         assert np.array_equal(val, ref.val)
+    plan.close()
+
+
+@pytest.mark.parametrize("c", [2, 5, 8, 9, 16])
+@pytest.mark.parametrize("sr", ["f64", "i64", "bool"])
+def test_merge_of_structure_alone(c, sr):
+    """Layers without values, merged without values, in every bin."""
+    print("case structure-only merge", c, sr, flush=True)
+    hl = [without_values(M) for M in merge_layers_of(c, 60 + c)]
+    ref = oracle.merge(hl, "bool")
+    plan = spg.Plan()
+    dev = [to_dev(M) for M in hl]
+    for got in (spg.spgemm_merge_layers(plan, sr, dev, values=False),
+                spg.spgemm_merge_layers_noalloc(sr, dev, values=False)):
+        rp, col, val = got.to_numpy()
+        assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col) and val is None
     plan.close()
