@@ -29,7 +29,7 @@ __device__ inline KwList<V> heap_lists(const Csr& A, const Csr& B, int64_t beg, 
         const int64_t bs = B.rp[kk];
         lst.start = bs;
         lst.len = (int32_t)(B.rp[kk + 1] - bs);
-        if (FILL) lst.scale = (A.val || SR == SR_BOOL) ? S::load(A.val, p) : S::zero();
+        if (FILL) lst.scale = S::load(A.val, p);
     }
     return lst;
 }

@@ -117,8 +117,7 @@ __device__ inline int32_t kway_merge_wave(const KwList<typename Sr<SR>::acc_t>& 
             const int64_t q = st + (x - lo);
             rc[u] = cp[q];
             if constexpr (FILL) {
-                // no value array: structure-only output (booleans: all true)
-                V v = (vp || SR == SR_BOOL) ? S::load(vp, q) : S::zero();
+                const V v = S::load(vp, q);
                 rv[u] = v;
                 if constexpr (SCALED) rv[u] = S::mul(sc, v);
             }

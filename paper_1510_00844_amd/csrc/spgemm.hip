@@ -1320,6 +1320,10 @@ extern "C" spg_status spgemm_numeric(spg_plan P, spg_semiring sr, const spg_csr*
     if (!P->num_counts_valid) SPG_TRY(read_counts(P, c_row_ptr, s.m, false));
     if (P->last_nnz > 0 && !c_col) return fail(SPG_ERR_ARG, "c_col is NULL");
     Csr a = view(A), b = view(B);
+    if (!c_val) {  // structure only: the operands need no values, so none are read
+        a.val = b.val = nullptr;
+        return numeric_sr<SR_BOOL>(P, a, b, c_row_ptr, c_col, nullptr);
+    }
     switch (sr) {
         case SPG_SR_PLUS_TIMES_F64: return numeric_sr<SR_F64>(P, a, b, c_row_ptr, c_col, c_val);
         case SPG_SR_PLUS_TIMES_I64: return numeric_sr<SR_I64>(P, a, b, c_row_ptr, c_col, c_val);

@@ -7,6 +7,7 @@ import pytest
 
 import oracle
 import paper_1510_00844_amd as spg
+import synth
 from gpu_util import to_dev
 from synth import CSR
 from synth.gen import canonical_from_coo
@@ -77,4 +78,40 @@ def test_merge_of_structure_alone(c, sr):
                 spg.spgemm_merge_layers_noalloc(sr, dev, values=False)):
         rp, col, val = got.to_numpy()
         assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col) and val is None
+    plan.close()
+
+
+PRODUCT_OPTS = {
+    "default": {},
+    "rank_chunks": dict(rank_max_nnz=1, chunk_min_nnz=1, dense_chunk_cols=2048),
+    "dense": dict(hash_max_nnz=64),
+    "heap": dict(heap_max_lists=32),
+}
+
+
+@pytest.mark.parametrize("opts", list(PRODUCT_OPTS))
+@pytest.mark.parametrize("sr", ["f64", "i64", "bool"])
+def test_product_structure_alone(opts, sr):
+    """Operands without values, multiplied without values: rows of one A entry
+    and more, of every accumulator, on both sides of the one-bitmap width, full and
+    windowed."""
+    print("case structure-only product", opts, sr, flush=True)
+    rng = np.random.default_rng(7)
+    A = synth.rmat(11, 8, synth.G500, seed=21)
+    wide = 700001
+    rows = np.repeat(np.arange(A.ncols), 6)
+    near = rng.integers(0, 40, (A.ncols, 1)) * 17000 + rng.integers(0, 900, (A.ncols, 6))
+    W = canonical_from_coo(A.ncols, wide, rows, near.ravel(), np.ones(rows.size), dup="first")
+    plan = spg.Plan(**PRODUCT_OPTS[opts])
+    bins = np.zeros(17, np.int64)
+    for B in (synth.rmat(11, 8, synth.SSCA, seed=22), W):
+        a, b = to_dev(without_values(A)), to_dev(without_values(B))
+        for lo, hi in ((0, A.ncols), (100, 1400)):
+            C = spg.spgemm(plan, sr, a, b, lo, hi, values=False)
+            bins += np.array(plan.stats()["num_rows"])
+            ref = oracle.spgemm(A, B, "bool", lo, hi, values=False)
+            assert C.val is None
+            assert np.array_equal(C.row_ptr.cpu().numpy(), ref.row_ptr) and np.array_equal(C.col.cpu().numpy(), ref.col)
+    assert bins[1] > 0 and bins[2] > 0  # the tiny and the small rows
+    assert {"default": bins[3:12].sum(), "rank_chunks": bins[11], "dense": bins[12], "heap": bins[16]}[opts] > 0
     plan.close()
