@@ -853,6 +853,8 @@ __device__ inline RankItem uniform_item(const RankItem& x) {
 constexpr int RANKC_NT = 512;
 constexpr int64_t RANKC_STATIC_LDS = (int64_t)(8 * ProductLds<RANKC_NT>::EB + sizeof(ProductLds<RANKC_NT>) +
                                                4 * (RANKC_NT / SPG_WAVE) + sizeof(RankItem)) + 64;
+// the dynamic LDS their kernel may take: declared to the runtime, and what bounds an item's size
+__host__ __device__ inline int64_t rankc_dyn_lds(int64_t max_lds) { return max_lds - RANKC_STATIC_LDS; }
 struct RankShape {
     int32_t RC, G;
 };

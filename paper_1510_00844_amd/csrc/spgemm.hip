@@ -374,6 +374,7 @@ template <int GM>
 static void set_lds_attributes(spg_plan P) {
     const int dyn_bitmap = std::max(0, P->max_lds - (int)sizeof(ProductLds<512>) - 64 - 4 * MAX_CHUNKS);
     const int dyn_rank = std::max(0, P->max_lds - RANK_STATIC_LDS);
+    const int dyn_rankc = std::max(0, (int)rankc_dyn_lds(P->max_lds));
     hipFuncSetAttribute((const void*)k_sym_bitmap<512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_bitmap);
     hipFuncSetAttribute((const void*)k_num_rank<SR_F64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
     hipFuncSetAttribute((const void*)k_num_rank<SR_I64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
@@ -382,12 +383,12 @@ static void set_lds_attributes(spg_plan P) {
     hipFuncSetAttribute((const void*)k_num_rank<SR_F64, 1024, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank_1024);
     hipFuncSetAttribute((const void*)k_num_rank<SR_I64, 1024, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank_1024);
     hipFuncSetAttribute((const void*)k_num_rank<SR_BOOL, 1024, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank_1024);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, GM, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, GM, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
     hipFuncSetAttribute((const void*)k_learned_fused<SR_F64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
     hipFuncSetAttribute((const void*)k_learned_fused<SR_I64, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
     hipFuncSetAttribute((const void*)k_learned_fused<SR_BOOL, 512, GM>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
@@ -396,14 +397,14 @@ static void set_lds_attributes(spg_plan P) {
 // gather mode 4 exists for the bitmap and rank-chunk kernels only
 static void set_lds_attributes_pipelined(spg_plan P) {
     const int dyn_bitmap = std::max(0, P->max_lds - (int)sizeof(ProductLds<512>) - 64 - 4 * MAX_CHUNKS);
-    const int dyn_rank = std::max(0, P->max_lds - RANK_STATIC_LDS);
+    const int dyn_rankc = std::max(0, (int)rankc_dyn_lds(P->max_lds));
     hipFuncSetAttribute((const void*)k_sym_bitmap<512, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_bitmap);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
-    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rank);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_F64, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_I64, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
+    hipFuncSetAttribute((const void*)k_num_rankc<SR_BOOL, RANKC_NT, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, dyn_rankc);
 }
 
 static int gather_mode(int map, int unroll) { return (map == 2 ? 2 : 0) + (unroll == 8 ? 1 : 0); }
@@ -1257,6 +1258,7 @@ static spg_status numeric_sr(spg_plan P, Csr a, Csr b, const int64_t* c_row_ptr,
             const int32_t* nitems = P->small_i32.as<int32_t>() + CTR_RANK_ITEMS;
             const int32_t nwords = (int32_t)((b.ncols + 31) / 32);
             const size_t lds = (size_t)G * (W / 32) * 6 + (size_t)RC * sizeof(typename Sr<SR>::acc_t);
+            if ((int64_t)lds > rankc_dyn_lds(P->max_lds)) return fail(SPG_ERR_HIP, "the LDS is too small for the rank-chunk items");
             const int32_t* split = chunks > 1 ? P->split.as<int32_t>() : nullptr;
             const unsigned grid = grid_for(std::min<int64_t>(nr * chunks, 256 * 8), 8) * 8;  // whole rounds of the XCDs
             const RankItem* items = P->rank_items.as<RankItem>();
