@@ -331,18 +331,18 @@ __device__ inline T block_reduce_add(T v, T* tmp) {
 }
 
 // ---------------------------------------------------------------------------
-// Bitonic sort of n (power of two) 64-bit keys in LDS, ascending, by NT
+// Bitonic sort of n (power of two) keys in LDS, ascending, by NT
 // threads.  Contains barriers.
 // ---------------------------------------------------------------------------
-template <int NT>
-__device__ inline void block_bitonic_sort_u64(uint64_t* keys, int n) {
+template <int NT, typename K>
+__device__ inline void block_bitonic_sort(K* keys, int n) {
     for (int k = 2; k <= n; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
             for (int t = threadIdx.x; t < (n >> 1); t += NT) {
                 // index of the lower element of the pair handled by t
                 int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
                 int p = i | j;
-                uint64_t a = keys[i], b = keys[p];
+                const K a = keys[i], b = keys[p];
                 bool up = (i & k) == 0;
                 if ((a > b) == up) {
                     keys[i] = b;

@@ -517,7 +517,7 @@ __global__ void __launch_bounds__(NT) k_num_hash(Csr A, Csr B, const int32_t* ro
     while (P < cnt) P <<= 1;
     for (int t = cnt + threadIdx.x; t < P; t += NT) skey[t] = ~0ull;
     __syncthreads();
-    block_bitonic_sort_u64<NT>(skey, P);
+    block_bitonic_sort<NT>(skey, P);
     for (int t = threadIdx.x; t < cnt; t += NT) rank_of[(int32_t)(skey[t] & 0xffffffffu)] = t;
     __syncthreads();
 #pragma unroll

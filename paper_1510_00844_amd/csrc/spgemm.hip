@@ -2868,7 +2868,8 @@ static spg_status restriction_sr(spg_plan P, int64_t n, int64_t na, const int32_
         k_sort_row_cols<<<grid_for(na, 4), 256, 0, cs(P)>>>(na, rt_rp, rt_col);
     }));
     SPG_TRY(launch(P, "sort_row_cols", [&] {
-        k_sort_long_row_cols<<<grid_for(na, SPG_WAVE), 256, 0, cs(P)>>>(na, rt_rp, rt_col, ctr + 2);
+        // (eight workgroups a CU: one round)
+        k_sort_long_row_cols<<<(unsigned)std::min<int64_t>(na, 8 * P->num_cu), 256, 0, cs(P)>>>(na, rt_rp, rt_col, ctr + 2);
     }));
     int32_t bad = 0;
     HIP_TRY(hipMemcpyAsync(&bad, ctr + 2, sizeof(int32_t), hipMemcpyDeviceToHost, P->stream));
