@@ -232,8 +232,14 @@ __device__ inline void walk_entries(const Csr& A, const Csr& B, int64_t lb, int6
 // that the dependent loads (row extent, A columns, B row extents) of both are
 // in flight together.  Bound by that latency: at most 512 workgroups (every
 // wave slot once, few statistics atomics), no barrier in the loop.
-__global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo, int64_t k_hi,
-                                                      int full_window, BinParams bp, RowInfoOut o) {
+// Runs of 2^run_log2 rows (4 to 64) are dealt out to the workgroups one after
+// another, so that long rows that lie side by side go to different ones: 64 rows
+// of 50,000 entries among 200,000 of 4, symbolic call 1745 us by runs of 64, 860
+// by 16, 645 by 4.  1000 rows of 3000 entries: 355 us on the 16 workgroups that
+// their number asks for, 153 on 250 (rowinfo_grid).
+constexpr int ROWINFO_RUN = 4;  // the shortest: a wave's rows
+__global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo, int64_t k_hi, int full_window,
+                                                      int run_log2, BinParams bp, RowInfoOut o) {
     constexpr int G = 16, NG = CLASS_NT / G, R = 2, E = 2;  // lanes a row, groups, rows a group, entries a lane
     constexpr int HUBS = 512;
     __shared__ ClassLds<2> c;
@@ -256,13 +262,16 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
         end = lower_bound_col(A.col, beg, end, k_hi);
     };
     const int64_t step = (int64_t)gridDim.x * NG;
-    for (int64_t i0 = (int64_t)blockIdx.x * NG; i0 < A.nrows; i0 += R * step) {
+    // the wave's first row of a step, and the group's of the wave's rows
+    const int g0 = g & ~(SPG_WAVE / G - 1), gr = g - g0, run = 1 << run_log2;
+    const int64_t first = (((int64_t)(g0 >> run_log2) * gridDim.x + blockIdx.x) << run_log2) + (g0 & (run - 1));
+    for (int64_t i0 = first; i0 < A.nrows; i0 += R * step) {
         int64_t beg[R], end[R], f[R];
         int32_t mb[R];
         bool active[R];
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            const int64_t i = i0 + u * step + g;
+            const int64_t i = i0 + u * step + gr;
             active[u] = i < A.nrows;
             beg[u] = active[u] ? A.rp[i] : 0;
             end[u] = active[u] ? A.rp[i + 1] : 0;
@@ -277,7 +286,7 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
             if (is_long && gl == 0 && end[u] - beg[u] > HUB_ROW) {
                 const int slot = atomicAdd(&s_nhub, 1);
                 if (slot < HUBS) {  // (past the queue's end: by the wave)
-                    s_hub[slot] = (int32_t)(i0 + u * step + g);
+                    s_hub[slot] = (int32_t)(i0 + u * step + gr);
                     hub = true;
                 }
             }
@@ -348,7 +357,7 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
                 const int32_t o2 = lane_xor(mb[u], d);
                 mb[u] = o2 > mb[u] ? o2 : mb[u];
             }
-            if (active[u] && gl == 0) finish(i0 + u * step + g, beg[u], end[u], f[u], mb[u]);
+            if (active[u] && gl == 0) finish(i0 + u * step + gr, beg[u], end[u], f[u], mb[u]);
             for (uint64_t m = longs[u]; m; m &= m - 1) {
                 const int l = __builtin_ctzll(m);
                 int64_t lb = lane_get(beg[u], l), le = lane_get(end[u], l);
@@ -358,7 +367,7 @@ __global__ void __launch_bounds__(CLASS_NT) k_rowinfo(Csr A, Csr B, int64_t k_lo
                 walk_entries(A, B, lb, le, lane, SPG_WAVE, lf, lm);
                 lf = wave_reduce_add(lf);
                 lm = wave_reduce_max(lm);
-                if (lane == l) finish(i0 + u * step + g, lb, le, lf, lm);
+                if (lane == l) finish(i0 + u * step + gr, lb, le, lf, lm);
             }
         }
     }

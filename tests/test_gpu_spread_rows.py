@@ -6,7 +6,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1510_00844_amd as spg
+from gpu_util import check_full_vs_oracle, to_dev
+from synth.gen import canonical_from_coo
 
 pytestmark = pytest.mark.gpu
 
@@ -54,4 +57,58 @@ def test_restriction_rows_of_every_sort(sizes):
     assert np.array_equal(RT.row_ptr.cpu().numpy(), np.concatenate([[0], np.cumsum(sizes)]))
     assert np.array_equal(RT.col.cpu().numpy(), np.argsort(agg, kind="stable"))
     assert np.array_equal(R.col.cpu().numpy(), agg)
+    plan.close()
+
+
+def rows_of_lengths(lens, K, seed):
+    """A matrix of K columns whose row i holds lens[i] entries."""
+    rng = np.random.default_rng(seed)
+    lens = np.asarray(lens)
+    cols = [rng.permutation(K)[:c] if c > 64 else rng.choice(K, c, replace=False) for c in lens[lens > 8]]
+    out = np.empty(lens.sum(), np.int64)
+    big = np.repeat(lens > 8, lens)
+    if cols:
+        out[big] = np.concatenate(cols)
+    out[~big] = (np.repeat(rng.integers(0, K, lens.size), lens) + 911 * (np.arange(lens.sum()) - np.repeat(np.cumsum(lens) - lens, lens)))[~big] % K
+    rows = np.repeat(np.arange(lens.size), lens)
+    return canonical_from_coo(lens.size, K, rows, out, rng.integers(1, 5, rows.size), dup="first")
+
+
+@pytest.mark.parametrize("name,one,many", [
+    ("hub rows among short ones", [30000] + [4] * 20000, [30000] * 64 + [4] * 20000),
+    ("few rows, all long", [3000] * 4, [3000] * 1000),
+])
+def test_row_analysis_of_long_rows_side_by_side(name, one, many):
+    K = 40009
+    B = to_dev(rows_of_lengths([2] * K, 5000, 1), "i64")
+    plan = spg.Plan(profile=True)
+    times = []
+    for lens in (one, many):
+        A = to_dev(rows_of_lengths(lens, K, 2), "i64")
+        times.append(kernel_ms(plan, "rowinfo", lambda: spg.spgemm_symbolic(plan, "i64", A, B)))
+    print("rowinfo, %s: %.4f ms, %.4f ms" % (name, *times))
+    assert times[1] < SPREAD * times[0]
+    plan.close()
+
+
+@pytest.mark.parametrize("m", [3, 1000, 262144, 262145, 300001])
+def test_row_analysis_deals_out_every_row(m):
+    """Rows of every length class at the first rows, the last and around the
+    runs, in numbers of rows on both sides of the longer runs; the bin counts see
+    every row once."""
+    K, n = 6000, 900
+    lens = np.ones(m, np.int64)
+    special = [5000, 2049, 2048, 129, 128, 0, 17, 300]
+    for base in (0, 12, 62, m // 2, m - 9):
+        for k, c in enumerate(special):
+            if 0 <= base + k < m:
+                lens[base + k] = c
+    A = rows_of_lengths(lens, K, 5)
+    B = rows_of_lengths([1, 0, 3] * (K // 3), n, 6)
+    plan = spg.Plan()
+    a, b = to_dev(A, "i64"), to_dev(B, "i64")
+    for lo, hi in ((0, K), (900, 5100)):
+        check_full_vs_oracle(spg.spgemm(plan, "i64", a, b, lo, hi), A, B, "i64", lo, hi)
+        st = plan.stats()
+        assert sum(st["sym_rows"]) == m and st["flops"] == oracle.row_flops(A, B, lo, hi).sum()
     plan.close()
