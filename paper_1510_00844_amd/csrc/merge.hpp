@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(256, 5) k_merge_sort(int32_t c, LayerSet layer
         cmin = __builtin_amdgcn_readfirstlane(wave_all(cmin, [](int32_t x, int32_t y) { return x < y ? x : y; }));
         cmax = __builtin_amdgcn_readfirstlane(wave_all(cmax, [](int32_t x, int32_t y) { return x > y ? x : y; }));
         wave_lds_sync();
-        wave_sort_row(W, L, cmin, cmax, col);
+        wave_sort_row(W, L, cmin, cmax, col, nullptr);
         (void)wave_fold_row<SR, NU>(W, L, cmin, out_col, out_val, o, room);
         wave_lds_sync();  // the row's LDS is read before the next row overwrites it
     }

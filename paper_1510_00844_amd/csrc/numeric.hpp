@@ -237,7 +237,7 @@ __device__ inline void num_sort_row(const Csr& A, const Csr& B, int64_t beg, int
     if (pos == 0) return;
     int32_t col[NU], cmin, cmax;
     wave_row_span(W, pos, col, cmin, cmax);
-    wave_sort_row(W, pos, cmin, cmax, col);
+    wave_sort_row(W, pos, cmin, cmax, col, reinterpret_cast<uint16_t*>(marks));  // (the marks are done with)
     (void)wave_fold_row<SR, NU>(W, pos, cmin, c_col, c_val, o, room);
 }
 

@@ -7,7 +7,14 @@
 // column and a value.  It becomes the key (column - cmin) << RS_XBITS | x; the
 // keys are counted into 64 buckets of equal column width (bucket = (column -
 // cmin) * 64 / span in FP32, monotone), placed bucket by bucket, and every
-// lane sorts its own bucket in registers with a sorting network.  Equal
+// lane sorts its own bucket in registers with a sorting network.  Columns in
+// clusters overflow the networks; product rows of a span that a bitmap in the
+// keys' place can hold then take buckets of equal numbers of columns, the others
+// a bitonic sort of the whole row.  12 runs of 32 neighbouring columns a row, in
+// a window of 12,000 (262,144 rows): numeric 1865 us by the whole-row sort, 1045
+// by the ranks, 930 hashed, where the hash table orders its outputs by such a
+// bitmap too; in 190,000 (131,072 rows): 935 by the whole-row sort, 3150 hashed.
+// Equal
 // columns are then neighbours in ascending x, so the fold adds them in that
 // order, and the output positions are counted by ballots: consecutive lanes
 // write consecutive outputs.
@@ -77,54 +84,106 @@ __device__ inline T wave_all(T v, Op op) {
     return v;
 }
 
-// W.key[x] holds the column of entry x < L (0 < L <= NU * 64) and spans fewer
-// than RS_SPAN_MAX columns from cmin to cmax; afterwards the sorted keys.
-// The caller's writes are visible (wave_lds_sync).
-template <int NU, typename V>
-__device__ inline void wave_sort_row(RowSortLds<V, NU>& W, int32_t L, int32_t cmin, int32_t cmax,
-                                     const int32_t (&col)[NU]) {
+// Counts the row's entries (bucket_of(u): step u's bucket) into W.bcnt, which
+// is clear, and sorts them if the largest bucket fits a network: the keys key_of(u)
+// are placed bucket by bucket and every lane sorts its own.  false: not sorted.
+// Counted first, then placed by a second atomic that returns the place: keeping
+// each entry's place in between costs registers, and so waves.
+template <int NU, typename V, class BucketOf, class KeyOf>
+__device__ inline bool wave_sort_by_buckets(RowSortLds<V, NU>& W, int32_t L, BucketOf bucket_of, KeyOf key_of) {
     const int lane = lane_id();
-    const float bscale = (float)SPG_WAVE / ((float)(uint32_t)(cmax - cmin) + 1.0f);
-    auto bucket = [&](int32_t c) {
-        const int32_t t = (int32_t)((float)(uint32_t)(c - cmin) * bscale);
-        return t < SPG_WAVE - 1 ? t : SPG_WAVE - 1;
-    };
-    // counted first, then placed by a second atomic that returns the place:
-    // keeping each entry's bucket and place in between cost 16 registers, and
-    // so waves
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
         if (u * SPG_WAVE >= L) break;
-        if (u * SPG_WAVE + lane < L) atomicAdd(&W.bcnt[bucket(col[u])], 1);
+        if (u * SPG_WAVE + lane < L) atomicAdd(&W.bcnt[bucket_of(u)], 1);
     }
     wave_lds_sync();
     const int32_t mine = W.bcnt[lane];
     const int32_t off = wave_inclusive_scan_add(mine) - mine;
-    const int32_t most = wave_all(mine, [](int32_t x, int32_t y) { return x > y ? x : y; });
-    if (__builtin_amdgcn_readfirstlane(most) <= RS_PAD) {
-        wave_lds_sync();  // every lane has its count
-        W.bcnt[lane] = off;
+    const int32_t most =
+        __builtin_amdgcn_readfirstlane(wave_all(mine, [](int32_t x, int32_t y) { return x > y ? x : y; }));
+    wave_lds_sync();  // every lane has its count
+    if (most > RS_PAD) return false;
+    W.bcnt[lane] = off;
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        if (u * SPG_WAVE >= L) break;
+        if (u * SPG_WAVE + lane < L) W.key[atomicAdd(&W.bcnt[bucket_of(u)], 1)] = key_of(u);
+    }
+    wave_lds_sync();
+    if (most <= 8) sort_bucket<8>(W.key, off, mine);
+    else if (most <= 12) sort_bucket<12>(W.key, off, mine);
+    else sort_bucket<16>(W.key, off, mine);
+    return true;
+}
+
+// Sorts entries x < L (0 < L <= NU * 64), col[u] the column of entry u * 64 +
+// lane, that span fewer than RS_SPAN_MAX columns from cmin to cmax, into W.key.
+// W.bcnt is clear; W.key may be overwritten.  pfx (optional): NU * 32 words for the
+// ranks of clustered columns.
+template <int NU, typename V>
+__device__ inline void wave_sort_row(RowSortLds<V, NU>& W, int32_t L, int32_t cmin, int32_t cmax,
+                                     const int32_t (&col)[NU], uint16_t* pfx) {
+    const int lane = lane_id();
+    auto key_of = [&](int u) { return ((uint32_t)(col[u] - cmin) << RS_XBITS) | (uint32_t)(u * SPG_WAVE + lane); };
+    const float bscale = (float)SPG_WAVE / ((float)(uint32_t)(cmax - cmin) + 1.0f);
+    bool done = wave_sort_by_buckets(W, L, [&](int u) {
+        const int32_t t = (int32_t)((float)(uint32_t)(col[u] - cmin) * bscale);
+        return t < SPG_WAVE - 1 ? t : SPG_WAVE - 1;
+    }, key_of);
+    // Clustered columns overfill some of the buckets of equal width.  Where a
+    // bitmap of the span fits W.key, a column's rank among the row's columns
+    // makes buckets of equal numbers of columns instead.
+    const int32_t nw = ((cmax - cmin) >> 5) + 1;
+    if (!done && pfx && nw <= NU * SPG_WAVE) {
+        static_assert(NU % 2 == 0, "a prefix for every two words");
+        W.bcnt[lane] = 0;
+#pragma unroll
+        for (int k = 0; k < NU; ++k) W.key[k * SPG_WAVE + lane] = 0;
         wave_lds_sync();
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             if (u * SPG_WAVE >= L) break;
-            const int32_t x = u * SPG_WAVE + lane;
-            if (x < L)
-                W.key[atomicAdd(&W.bcnt[bucket(col[u])], 1)] = ((uint32_t)(col[u] - cmin) << RS_XBITS) | (uint32_t)x;
+            const int32_t d = col[u] - cmin;
+            if (u * SPG_WAVE + lane < L) atomicOr(&W.key[d >> 5], 1u << (d & 31));
         }
         wave_lds_sync();
-        const int32_t m = __builtin_amdgcn_readfirstlane(most);
-        if (m <= 8) sort_bucket<8>(W.key, off, mine);
-        else if (m <= 12) sort_bucket<12>(W.key, off, mine);
-        else sort_bucket<16>(W.key, off, mine);
-    } else {
-        // a larger bucket (clustered columns): the wave sorts the row whole
+        int32_t two[NU / 2], sum = 0;  // set bits of this lane's pairs of words
+#pragma unroll
+        for (int k = 0; k < NU / 2; ++k) {
+            two[k] = __popc(W.key[lane * NU + 2 * k]) + __popc(W.key[lane * NU + 2 * k + 1]);
+            sum += two[k];
+        }
+        const int32_t incl = wave_inclusive_scan_add(sum);
+        int32_t run = incl - sum;
+#pragma unroll
+        for (int k = 0; k < NU / 2; ++k) {
+            pfx[lane * (NU / 2) + k] = (uint16_t)run;
+            run += two[k];
+        }
+        wave_lds_sync();
+        const float rscale = (float)SPG_WAVE / (float)__builtin_amdgcn_readlane(incl, SPG_WAVE - 1);
+        uint32_t b[NU];  // the entries' buckets
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            if (u * SPG_WAVE >= L) break;
+            const int32_t d = col[u] - cmin, w = d >> 5;
+            const uint32_t below = W.key[w] & ((1u << (d & 31)) - 1u), before = W.key[w & ~1];
+            const int32_t rank = (int32_t)pfx[w >> 1] + __popc(below) + ((w & 1) ? __popc(before) : 0);
+            const int32_t t = (int32_t)((float)rank * rscale);
+            b[u] = t < SPG_WAVE - 1 ? t : SPG_WAVE - 1;
+        }
+        wave_lds_sync();  // the bitmap is read before keys overwrite it
+        done = wave_sort_by_buckets(W, L, [&](int u) { return b[u]; }, key_of);
+    }
+    if (!done) {  // the wave sorts the row whole
         int P = SPG_WAVE;
         while (P < L) P <<= 1;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const int32_t x = u * SPG_WAVE + lane;
-            if (x < L) W.key[x] = ((uint32_t)(col[u] - cmin) << RS_XBITS) | (uint32_t)x;
+            if (x < L) W.key[x] = key_of(u);
             else if (x < P) W.key[x] = 0xffffffffu;
         }
         wave_lds_sync();
