@@ -3,14 +3,14 @@
 // output is the sorted union of the c sorted segments layer_l(i,:), with
 // values of equal columns combined in ascending layer order.  The paper
 // merges with a heap per thread over a split of the column range; here:
-//   SORT   (more than 4 layers) rows of 65 ... MS_LMAX entries whose columns
+//   SORT   (merge_sorts) rows of 65 ... MS_LMAX entries whose columns
 //          span less than RS_SPAN_MAX: one wave per row sorts the entries
 //          by column and layer (rowsort.hpp) and folds equal columns in
 //          ascending layer order
 //   WAVE   rows of at most KW_LMAX entries over at most 8 layers: one
 //          wave per row, the column range split over the 64 lanes and each
 //          lane merging its range of the c segments (kway.hpp), staged in LDS
-//   SMALL  (more than 4 layers) rows of <= 64 entries: a wave sort of
+//   SMALL  (merge_sorts) rows of <= 64 entries: a wave sort of
 //          (column, position)
 //   RANK   65 ... 4096 entries: a workgroup places each entry by binary
 //          searches in the other layers' segments, staged in LDS
@@ -51,20 +51,28 @@ constexpr int MERGE_LDS_MAX = 4096;
 // layers the wave k-way merge takes (it costs O(c) instructions per output)
 constexpr int MERGE_KWAY_MAX_LAYERS = 8;
 
-// Rows whose columns pack (see RS_SPAN_MAX) are sorted from five layers on: the
-// cost of the k-way sweep grows with the layers (ER scale 18, 256 entries a row,
-// count and fill: two layers 0.93 ms by either, four 1.06 against 1.00 by the
-// sort, eight 1.52 against 1.02).  At three and four layers the sort's lead is
-// lost on rows of mixed lengths, where it needs bins of its own (SSCA scale 15,
-// four layers: 0.33 against 0.29).  Rows of up to 64 entries take the register
-// sort (25 entries a row, eight layers: 0.30 against 0.38 by the sweep).
-__device__ inline int64_t merge_sort_min(int c) {  // rows of more entries are sorted
-    return c <= 4 ? MS_LMAX : SPG_WAVE;
+// Whether rows are sorted: rows of up to 64 entries by the register sort, longer
+// ones whose columns pack (see RS_SPAN_MAX) by the row sort.  Never up to four
+// layers, always above eight.  The cost of the k-way sweep grows with the layers
+// (ER scale 18, 256 entries a row, count and fill: two layers 0.93 ms by either,
+// four 1.06 against 1.00 by the sort, eight 1.52 against 1.02); at three and four
+// the sort's lead is lost on rows of mixed lengths, where it needs bins of its own
+// (SSCA scale 15, four layers: 0.33 against 0.29).  From five to eight the two
+// bins also need enough rows to hide their latency and their launches: as
+// measured in us, sorted / swept, eight layers: 256 entries a row (ER) 8192 rows
+// 151 / 144, 16384 185 / 187, 32768 234 / 268; 16 a row 4096 rows 72 / 70, 8192
+// 74 / 80, 16384 78 / 97; and where the mean row is longer than the sweep takes
+// (SSCA, G500), few rows are sorted at all: 2048 rows 302 / 268, 16384 534 / 521,
+// 65536 2616 / 2630.
+inline bool merge_sorts(int32_t c, int64_t m, int64_t entries) {
+    if (c <= 4 || c > MERGE_KWAY_MAX_LAYERS) return c > 4;
+    if (entries > KW_LMAX * m) return false;
+    return m >= (entries <= SPG_WAVE * m ? 1 << 13 : 1 << 14);
 }
 
-__device__ inline int merge_bin(int64_t L, int c) {
+__device__ inline int merge_bin(int64_t L, int c, bool sorts) {
     if (L == 0) return MBIN_EMPTY;
-    if (L <= SPG_WAVE && c > 4) return MBIN_SMALL;
+    if (L <= SPG_WAVE && sorts) return MBIN_SMALL;
     if (L <= KW_LMAX && c <= MERGE_KWAY_MAX_LAYERS) return MBIN_WAVE;
     if (L <= 256) return MBIN_R256;
     if (L <= 1024) return MBIN_R1K;
@@ -75,7 +83,7 @@ __device__ inline int merge_bin(int64_t L, int c) {
 // packs: every span of the n columns packs (n <= MS_SPAN_MAX), so no column is
 // read (the two ends of every segment were most of this kernel's time: 67 -> 28
 // us for 16 layers of 262,144 rows).
-__global__ void __launch_bounds__(256) k_merge_rowinfo(int64_t m, int32_t c, LayerSet layers, int packs,
+__global__ void __launch_bounds__(256) k_merge_rowinfo(int64_t m, int32_t c, LayerSet layers, int sorts, int packs,
                                                        int64_t* total_len, uint8_t* bin,
                                                        int64_t* bin_stats) {
     __shared__ int s_hist[NBINS];
@@ -89,8 +97,8 @@ __global__ void __launch_bounds__(256) k_merge_rowinfo(int64_t m, int32_t c, Lay
         int64_t L = 0;
         for (int l = 0; l < c; ++l) L += layers.d[l].rp[i + 1] - layers.d[l].rp[i];
         total_len[i] = L;
-        int b = merge_bin(L, c);
-        if (L > merge_sort_min(c) && L <= MS_LMAX) {  // the bucket sort, if the columns pack
+        int b = merge_bin(L, c, sorts != 0);
+        if (sorts && L > SPG_WAVE && L <= MS_LMAX) {  // the bucket sort, if the columns pack
             int32_t mn = packs ? 0 : 0x7fffffff, mx = packs ? 0 : -1;
             for (int l = 0; l < c && !packs; ++l) {
                 const int64_t rs = layers.d[l].rp[i], re = layers.d[l].rp[i + 1];

@@ -1450,15 +1450,18 @@ static LayerSet layer_set(int32_t nlayers, const spg_csr* layers) {
 
 // Row analysis of the merge: total lengths, bins, per-bin lists; then the
 // bin counts are read back (synchronizing) into counts[MBINS].
-static spg_status merge_classify(spg_plan P, int32_t c, const LayerSet& ls, int64_t m, int64_t n, int64_t* tl, uint8_t* mbin,
-                                 int32_t* mlists, int64_t* mstats, int32_t* mctr, int64_t* counts,
+static spg_status merge_classify(spg_plan P, int32_t c, const spg_csr* layers, const LayerSet& ls, int64_t* tl,
+                                 uint8_t* mbin, int32_t* mlists, int64_t* mstats, int32_t* mctr, int64_t* counts,
                                  int64_t* host_buf) {
+    const int64_t m = layers[0].nrows, n = layers[0].ncols;
+    int64_t entries = 0;
+    for (int l = 0; l < c; ++l) entries += layers[l].nnz;
     SPG_TRY(fill_i64(P, mstats, 2 * NBINS, 0));
     SPG_TRY(fill_i32(P, mctr, NBINS, 0));
     if (m > 0) {
         SPG_TRY(launch(P, "merge_rowinfo", [&] {
             k_merge_rowinfo<<<(unsigned)std::min<int64_t>(grid_for(m, 256), 1024), 256, 0, cs(P)>>>(
-                m, c, ls, n <= MS_SPAN_MAX ? 1 : 0, tl, mbin, mstats);
+                m, c, ls, merge_sorts(c, m, entries) ? 1 : 0, n <= MS_SPAN_MAX ? 1 : 0, tl, mbin, mstats);
         }));
         SPG_TRY(launch(P, "bin_scatter", [&] {
             k_bin_scatter<<<grid_for(m, CLASS_NT), CLASS_NT, 0, cs(P)>>>(
@@ -1495,7 +1498,7 @@ extern "C" spg_status spgemm_merge_layers(spg_plan P, spg_semiring sr, int32_t n
         SPG_TRY(P->mlists.ensure(4 * mm, "merge lists"));
         SPG_TRY(P->mstats.ensure(sizeof(int64_t) * 4 * NBINS, "merge stats"));
         SPG_TRY(P->mctr.ensure(sizeof(int32_t) * 64, "merge counters"));
-        SPG_TRY(merge_classify(P, nlayers, ls, m, n, P->merge_len.as<int64_t>(), P->mbin.as<uint8_t>(),
+        SPG_TRY(merge_classify(P, nlayers, layers, ls, P->merge_len.as<int64_t>(), P->mbin.as<uint8_t>(),
                                P->mlists.as<int32_t>(), P->mstats.as<int64_t>(), P->mctr.as<int32_t>(), P->merge_counts,
                                P->h_stats));
         P->merge_sig = desc;
@@ -1615,7 +1618,7 @@ extern "C" spg_status spgemm_merge_layers_noalloc(void* stream, spg_semiring sr,
     const LayerSet ls = layer_set(nlayers, layers);
     int64_t counts[2 * NBINS] = {};
     // each pass classifies the rows itself, so no state is kept between calls
-    SPG_TRY(merge_classify(&T, nlayers, ls, m, layers[0].ncols, L.tl, L.mbin, L.mlists, L.mstats, L.mctr, counts, host_buf));
+    SPG_TRY(merge_classify(&T, nlayers, layers, ls, L.tl, L.mbin, L.mlists, L.mstats, L.mctr, counts, host_buf));
     if (count_pass) {
         int64_t* cnt = out_row_ptr + 1;
         SPG_TRY(fill_i64(&T, cnt, m, 0));
