@@ -84,6 +84,32 @@ __device__ inline int num_bin(int64_t flops, int64_t annz, int64_t cnt, bool sym
     return chunks_ok ? BIN_DENSE_PAR : BIN_DENSE;
 }
 
+// Whether a product's kernels are spread over the helper streams at all, from
+// the counts of a classification ([0, NBINS) rows, [NBINS, 2 NBINS) products) that
+// launches a kernel for every bin with rows from first_bin on.  A fork and a join
+// cost ten calls on the host and waits between the GPU's queues, 20 to 50 us a
+// phase; what they save is the latency of each further kernel, which is that of a
+// few rows however many it has: a bin's share of the work says little.  So: from six
+// kernels on (power-law matrices; uniform ones and stencils have fewer), and not
+// for few products.  One decision for both passes, from the symbolic bins: with
+// one pass spread and the other not, each was slower than alone (ER 21,083 x 55,716
+// x 32,369: 230 us both spread, 243 neither, 272 the symbolic pass only).
+// Gain of four streams over one, whole products of random graphs of 1M to 400M
+// products, us by symbolic kernels: two to four -69 to -42, five -50 to -21, six -96
+// to 57, seven and more -26 to 193 (R-MAT scale 16, eight: 1948 -> 1924; the
+// rectangular boolean product, seven: 516 -> 470).
+constexpr int64_t FORK_MIN_PRODUCTS = 1 << 20;
+constexpr int FORK_MIN_KERNELS = 6;
+inline bool worth_forking(const int64_t* counts, int first_bin) {
+    int64_t products = 0;
+    int kernels = 0;
+    for (int b = BIN_TINY; b < NBINS; ++b) {
+        products += counts[NBINS + b];
+        kernels += b >= first_bin && counts[b] > 0;
+    }
+    return products >= FORK_MIN_PRODUCTS && kernels >= FORK_MIN_KERNELS;
+}
+
 // The rows of one bin, located on the device: the per-bin row counts (the
 // lists of the bins below b come first in `lists`).  Kernels launched this
 // way stride over the bin's rows, so their launches need no host copy of

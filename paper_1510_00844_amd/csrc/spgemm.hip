@@ -139,6 +139,7 @@ struct spg_plan_s {
     // calls can be captured into a HIP graph)
     bool frozen = false;
     bool have_symbolic = false;
+    bool spread = false;        // the product's kernels run on the helper streams too (decided by the symbolic pass)
     bool num_counts_valid = false;
     int64_t sym_counts[3 * NBINS];
     int64_t num_counts[4 * NBINS];
@@ -232,25 +233,6 @@ static spg_status join_streams(spg_plan P, int naux) {
     P->cur = nullptr;
     return SPG_OK;
 }
-// Whether a phase's bins are spread over the helper streams at all.  A fork
-// and a join cost ten calls on the host and waits between the GPU's queues,
-// about 50 us a phase measured; what they save is the ramp and the tail of
-// each kernel that does not fill the GPU.  So: from six bins with rows on
-// (power-law matrices; uniform ones and stencils have fewer, and their one or
-// two large bins fill the GPU by themselves), and not for few products.
-// One stream against four: 65,536 products 72 / 179 us; ER scale 18 (5 bins)
-// 1170 / 1203; R-MAT scale 16 (12 bins) 1926 / 1729.
-static const int64_t FORK_MIN_PRODUCTS = 1 << 20;
-static const int FORK_MIN_BINS = 6;
-static bool worth_forking(const int64_t* counts) {
-    int64_t products = 0;
-    int bins = 0;
-    for (int b = 1; b < NBINS; ++b) {
-        products += counts[NBINS + b];
-        bins += counts[b] > 0;
-    }
-    return products >= FORK_MIN_PRODUCTS && bins >= FORK_MIN_BINS;
-}
 // Bins go to streams longest-processing-time first: each bin (in order of
 // decreasing work) to the stream with the least work so far; the first
 // serial_heavy bins stay on the plan's stream.  Work = products + 32 per row.
@@ -265,7 +247,7 @@ static double bin_work(const int64_t* counts, int bin) {
 struct StreamLoad {
     double load[NAUX + 1] = {};
     int nstreams = 1;
-    StreamLoad(spg_plan P, const int64_t* counts) {
+    StreamLoad(spg_plan P, const int64_t* counts, bool spread) {
         double total = 0;
         for (int b = 1; b < NBINS; ++b) total += bin_work(counts, b);
         int heavy = 0;
@@ -274,7 +256,7 @@ struct StreamLoad {
         int nonempty = 0;
         for (int b = 1; b < NBINS; ++b) nonempty += counts[b] > 0;
         nstreams = std::max(1, std::min(P->opts.streams, std::max(heavy, nonempty > 1 ? 2 : 1)));
-        if (!worth_forking(counts)) nstreams = 1;
+        if (!spread) nstreams = 1;
     }
 };
 static void use_stream(spg_plan P, StreamLoad& L, int pos, const int64_t* counts, int bin) {
@@ -1017,7 +999,8 @@ static spg_status symbolic_pass(spg_plan P, spg_semiring sr, const spg_csr* A, c
     // per-bin accumulators: the bitmap rows (heaviest first) on the plan's
     // stream, the other bins round robin over the helper streams
     int nstreams = std::max(1, std::min(P->opts.streams, NAUX + 1));
-    if (!worth_forking(hint)) nstreams = 1;
+    P->spread = worth_forking(hint, BIN_SMALL);  // (rows of one A entry need no symbolic kernel)
+    if (!P->spread) nstreams = 1;
     SPG_TRY(fork_streams(P, nstreams - 1));
     // the numeric pass's split table (B and W only) on the last helper stream
     // when rank-chunk items are possible (chunk counts recorded, bitmap rows
@@ -1222,7 +1205,7 @@ static spg_status numeric_sr(spg_plan P, Csr a, Csr b, const int64_t* c_row_ptr,
         P->split_ready = true;
     }
     const std::vector<int> num_order = bins_by_work(P->num_counts, P->num_counts + NBINS);
-    StreamLoad nload(P, P->num_counts);
+    StreamLoad nload(P, P->num_counts, P->spread);
     SPG_TRY(fork_streams(P, nload.nstreams - 1));
     for (size_t oi = 0; oi < num_order.size(); ++oi) {
         const int bb = num_order[oi];
@@ -2035,7 +2018,7 @@ static spg_status learned_launch(spg_plan P, Csr a, Csr b, int32_t nwords) {
     bin_off[0] = 0;
     for (int x = 0; x < NBINS; ++x) bin_off[x + 1] = bin_off[x] + P->l_counts[x];
     const std::vector<int> order = bins_by_work(P->l_counts, P->l_counts + NBINS);
-    StreamLoad lload(P, P->l_counts);
+    StreamLoad lload(P, P->l_counts, worth_forking(P->l_counts, BIN_TINY));
     SPG_TRY(fork_streams(P, lload.nstreams - 1));
     for (size_t oi = 0; oi < order.size(); ++oi) {
         const int bb = order[oi];
