@@ -87,7 +87,9 @@ typedef struct {
     int32_t hash_max_nnz;      /* numeric: LDS hash table up to this many outputs per row */
     int32_t dense_chunk_cols;  /* numeric dense rows: columns per LDS chunk (2048, 4096, 8192 or 16384) */
     int32_t profile;           /* 1: time every kernel launch with HIP events */
-    int32_t streams;           /* streams independent bins are spread over (1..4) */
+    int32_t streams;           /* streams independent bins are spread over (1..4), at most: products of
+                                  fewer than 2^20 scalar products or fewer than six symbolic kernels
+                                  run on the plan's stream alone */
     int32_t gather_map;        /* numeric heavy rows, products per lane: 1 = neighbouring lanes take
                                   neighbouring products (coalesced), 2 = each lane a contiguous range */
     int32_t unroll;            /* numeric heavy rows: gathers in flight per lane (4 or 8) */
@@ -101,10 +103,11 @@ typedef struct {
     int32_t rank_max_nnz;      /* numeric rows with a saved bitmap and at most this many outputs
                                   accumulate the whole row in one workgroup (capacities 4096, 8192,
                                   16384 as the LDS allows; below 4096: never) */
-    int32_t rank_block;        /* threads per workgroup of the whole-row rank accumulator: 512 (the
-                                  default: shares the CUs better with the rank-chunk kernel beside it)
-                                  or 1024 (more loads in flight, faster alone; capacity 16384 only when
-                                  the LDS allows it) */
+    int32_t rank_block;        /* threads per workgroup of the whole-row rank accumulator: 512 (shares the
+                                  CUs better with the rank-chunk kernel beside it), 1024 (more loads in
+                                  flight, faster alone; capacity 16384 only when the LDS allows it) or 0
+                                  = the default: 512, and 1024 for the capacities of which a CU's LDS
+                                  holds only one workgroup */
     int32_t serial_heavy;      /* the this-many bins with the most work run back to back on the plan's
                                   stream; the other bins are spread over the streams (0..16) */
     int32_t chunk_unroll;      /* gathers in flight per lane in the rank-chunk items (4 or 8) */

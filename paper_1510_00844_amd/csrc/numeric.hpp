@@ -820,6 +820,18 @@ __global__ void __launch_bounds__(NT) k_num_rank(Csr A, Csr B, const int32_t* ro
     if (c_val) write_values<SR, NT>(acc, cnt, c_val, off);
 }
 
+// static LDS of k_num_rank<*, 512> and <*, 1024> (A values, product offsets, scan scratch), with margin
+constexpr int RANK_STATIC_LDS = (int)(8 * 512 + sizeof(ProductLds<512>) + 4 * 16 + 256);
+constexpr int RANK_STATIC_LDS_1024 = (int)(8 * 1024 + sizeof(ProductLds<1024>) + 4 * 32 + 256);
+
+// Threads of k_num_rank at `lds` bytes of dynamic LDS: what the option asks for,
+// or (0) 512, and 1024 where a CU holds only one workgroup of 512.
+inline int rank_threads(int32_t rank_block, int64_t lds, int64_t max_lds) {
+    const bool one = 2 * (lds + RANK_STATIC_LDS) > max_lds;
+    const bool wide = rank_block == 1024 || (rank_block == 0 && one);
+    return wide && lds + RANK_STATIC_LDS_1024 <= max_lds ? 1024 : 512;
+}
+
 // Rank chunks: the rows of the bitmap pass that are too large for the
 // per-row rank kernel.  A row's column chunks of W columns (counts recorded
 // by the bitmap pass) are grouped greedily into items of at most RC outputs

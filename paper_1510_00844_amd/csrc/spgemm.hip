@@ -295,9 +295,6 @@ static inline int rowinfo_run_log2(int64_t m) { return m <= (1 << 18) ? 2 : 4; }
 // Numeric classification: a tile of CLASS_NT rows per workgroup step.
 static inline unsigned classify_grid(int64_t m) { return (unsigned)std::min<int64_t>(grid_for(m, CLASS_NT), 128); }
 
-// static LDS of k_num_rank<*, 512> (A values, product offsets, scan scratch), with margin
-static const int RANK_STATIC_LDS = (int)(8 * 512 + sizeof(ProductLds<512>) + 4 * 16 + 256);
-static const int RANK_STATIC_LDS_1024 = (int)(8 * 1024 + sizeof(ProductLds<1024>) + 4 * 32 + 256);
 static int rank_static_lds(spg_plan P) { return P->opts.rank_block == 1024 ? RANK_STATIC_LDS_1024 : RANK_STATIC_LDS; }
 // small counters and flags (int32), one size, never reallocated:
 //   [0, 8)      the CSR check flag, the learned mode's and the stages' counters
@@ -338,7 +335,7 @@ extern "C" void spg_default_opts(spg_opts* o) {
     o->chunk_min_nnz = 0;  // = hash_max_nnz
     o->chunk_group = 32;
     o->rank_max_nnz = 8192;
-    o->rank_block = 512;
+    o->rank_block = 0;  // by the row's LDS
     o->chunk_unroll = 4;
     o->heap_max_lists = -1;  // off: slower than the hash tables on the workloads measured here
 }
@@ -461,7 +458,6 @@ extern "C" spg_status spg_plan_create(spg_plan* out, void* stream, const spg_opt
         if (!P->opts.chunk_min_nnz) P->opts.chunk_min_nnz = P->opts.hash_max_nnz;
         if (!P->opts.chunk_group) P->opts.chunk_group = d.chunk_group;
         if (!P->opts.rank_max_nnz) P->opts.rank_max_nnz = d.rank_max_nnz;
-        if (!P->opts.rank_block) P->opts.rank_block = d.rank_block;
         if (!P->opts.chunk_unroll) P->opts.chunk_unroll = d.chunk_unroll;
         if (!P->opts.heap_max_lists) P->opts.heap_max_lists = d.heap_max_lists;
     }
@@ -505,9 +501,9 @@ extern "C" spg_status spg_plan_create(spg_plan* out, void* stream, const spg_opt
         delete P;
         return fail(SPG_ERR_ARG, "serial_heavy must be in [0, 16]");
     }
-    if (P->opts.rank_block != 512 && P->opts.rank_block != 1024) {
+    if (P->opts.rank_block != 0 && P->opts.rank_block != 512 && P->opts.rank_block != 1024) {
         delete P;
-        return fail(SPG_ERR_ARG, "rank_block must be 512 or 1024");
+        return fail(SPG_ERR_ARG, "rank_block must be 512, 1024 or 0 (by the row's LDS)");
     }
     if (P->opts.chunk_min_nnz < 1 || P->opts.chunk_min_nnz > P->opts.hash_max_nnz || P->opts.chunk_group < 1 ||
         P->opts.chunk_group > MAX_CHUNKS) {
@@ -1225,11 +1221,10 @@ static spg_status numeric_sr(spg_plan P, Csr a, Csr b, const int64_t* c_row_ptr,
             const int32_t nwords = (int32_t)((b.ncols + 31) / 32);
             const int64_t cap = 4096ll << (bb - BIN_RANK0);
             const size_t lds = (size_t)nwords * 6 + (size_t)cap * sizeof(typename Sr<SR>::acc_t);
-            // 1024 threads where a CU holds only one workgroup of 512
-            const bool wide = P->opts.rank_block == 1024 || 2 * ((int64_t)lds + RANK_STATIC_LDS) > P->max_lds;
+            const bool wide = rank_threads(P->opts.rank_block, (int64_t)lds, P->max_lds) == 1024;
             SPG_TRY(with_gm(P, [&](auto gm) {
                 return launch(P, "num_rank" + std::to_string(cap), [&] {
-                    if (wide && (int64_t)lds + RANK_STATIC_LDS_1024 <= P->max_lds)
+                    if (wide)
                         k_num_rank<SR, 1024, decltype(gm)::value><<<(unsigned)nr, 1024, lds, cs(P)>>>(
                             a, b, rows, ab, ae, P->bm_save.as<uint32_t>(), P->heavy_idx.as<int32_t>(), nwords, (int32_t)cap,
                             crp, ccol, cval);
