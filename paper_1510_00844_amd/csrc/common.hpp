@@ -240,6 +240,18 @@ __device__ inline T wave_reduce_max(T v) {
     return v;
 }
 
+// Every lane's value combined by op, in all lanes (written out: as a loop the
+// exchanges' switch over the distance kept the compiler from unrolling it).
+template <typename T, class Op>
+__device__ inline T wave_all(T v, Op op) {
+    v = op(v, lane_xor(v, 32));
+    v = op(v, lane_xor(v, 16));
+    v = op(v, lane_xor(v, 8));
+    v = op(v, lane_xor(v, 4));
+    v = op(v, lane_xor(v, 2));
+    return op(v, lane_xor(v, 1));
+}
+
 // Number of set lanes strictly below this lane in a 64-bit mask.
 __device__ inline int lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),

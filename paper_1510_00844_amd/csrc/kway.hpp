@@ -139,12 +139,8 @@ __device__ inline int32_t kway_merge_wave(const KwList<typename Sr<SR>::acc_t>& 
         cmin = W.col[soff];
         cmax = W.col[soff + len - 1];
     }
-#pragma unroll
-    for (int d = SPG_WAVE / 2; d > 0; d >>= 1) {
-        const int32_t a = lane_xor(cmin, d), b = lane_xor(cmax, d);
-        cmin = a < cmin ? a : cmin;
-        cmax = b > cmax ? b : cmax;
-    }
+    cmin = wave_all(cmin, [](int32_t x, int32_t y) { return x < y ? x : y; });
+    cmax = wave_all(cmax, [](int32_t x, int32_t y) { return x > y ? x : y; });
     if (cmax < 0) return 0;  // no entries
     const int64_t span = (int64_t)cmax - cmin + 1;
     const int64_t width = (span + SPG_WAVE - 1) / SPG_WAVE;

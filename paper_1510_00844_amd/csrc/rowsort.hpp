@@ -77,13 +77,6 @@ __device__ inline void sort_bucket(uint32_t* keys, int32_t off, int32_t n) {
         if (u < n) keys[off + u] = a[u];
 }
 
-template <typename T, class Op>
-__device__ inline T wave_all(T v, Op op) {
-#pragma unroll
-    for (int d = SPG_WAVE / 2; d > 0; d >>= 1) v = op(v, lane_xor(v, d));
-    return v;
-}
-
 // Counts the row's entries (bucket_of(u): step u's bucket) into W.bcnt, which
 // is clear, and sorts them if the largest bucket fits a network: the keys key_of(u)
 // are placed bucket by bucket and every lane sorts its own.  false: not sorted.
