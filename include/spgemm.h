@@ -76,7 +76,8 @@ typedef struct {
     int64_t nnz;
     const int64_t* row_ptr; /* device, nrows+1 */
     const int32_t* col;     /* device, nnz */
-    const void* val;        /* device, nnz; NULL allowed only for the boolean semiring */
+    const void* val;        /* device, nnz; NULL allowed for the boolean semiring, and for any
+                               where a call is asked for the structure only */
 } spg_csr;
 
 /* Tuning options.  Zero fields take the defaults of spg_default_opts(). */
@@ -402,7 +403,7 @@ spg_status spg_autotune_galerkin(spg_plan plan, spg_semiring sr, int32_t nb, con
  * with the smallest SplitMix64 choice key.
  * in_mis: device, n bytes (1 = in the set); agg: device, n int32 aggregate
  * numbers; *n_agg (host): number of aggregates; *rounds (host, may be
- * NULL): rounds taken.  Synchronizes every round.  SPG_ERR_SHAPE if A is
+ * NULL): rounds taken.  Synchronizes every four rounds.  SPG_ERR_SHAPE if A is
  * not square; SPG_ERR_STATE if the rounds do not end (asymmetric pattern).
  * ------------------------------------------------------------------------ */
 spg_status spg_mis2_aggregate(spg_plan plan, const spg_csr* A, uint64_t seed, uint8_t* in_mis, int32_t* agg,

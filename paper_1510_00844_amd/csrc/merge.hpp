@@ -54,16 +54,16 @@ constexpr int MERGE_KWAY_MAX_LAYERS = 8;
 // Whether rows are sorted: rows of up to 64 entries by the register sort, longer
 // ones whose columns pack (see RS_SPAN_MAX) by the row sort.  Never up to four
 // layers, always above eight.  The cost of the k-way sweep grows with the layers
-// (ER scale 18, 256 entries a row, count and fill: two layers 0.93 ms by either,
-// four 1.06 against 1.00 by the sort, eight 1.52 against 1.02); at three and four
-// the sort's lead is lost on rows of mixed lengths, where it needs bins of its own
-// (SSCA scale 15, four layers: 0.33 against 0.29).  From five to eight the two
-// bins also need enough rows to hide their latency and their launches: as
-// measured in us, sorted / swept, eight layers: 256 entries a row (ER) 8192 rows
-// 151 / 144, 16384 185 / 187, 32768 234 / 268; 16 a row 4096 rows 72 / 70, 8192
-// 74 / 80, 16384 78 / 97; and where the mean row is longer than the sweep takes
-// (SSCA, G500), few rows are sorted at all: 2048 rows 302 / 268, 16384 534 / 521,
-// 65536 2616 / 2630.
+// (ER scale 18, 256 entries a row, count and fill, swept / sorted: two layers 0.93
+// / 0.86 ms, four 1.01 / 0.87, eight 1.52 / 0.89).  Up to four, what the sort gains
+// on many uniform rows it loses on few of them (ER scale 14, four layers: 141 / 161
+// us) and on rows of mixed lengths (SSCA scale 11 162 / 193, scale 15 761 / 781),
+// where it needs bins of its own.  From five to eight the two bins also need
+// enough rows to hide their latency and their launches; eight layers, swept /
+// sorted: 256 entries a row (ER) 8192 rows 144 / 154 us, 16384 187 / 177, 32768
+// 268 / 219; 16 a row 4096 rows 71 / 74, 8192 80 / 77, 16384 97 / 84; and where
+// the mean row is longer than the sweep takes (SSCA, G500), few rows are sorted at
+// all: 2048 rows 269 / 300, 16384 526 / 544, 65536 2602 / 2597.
 inline bool merge_sorts(int32_t c, int64_t m, int64_t entries) {
     if (c <= 4 || c > MERGE_KWAY_MAX_LAYERS) return c > 4;
     if (entries > KW_LMAX * m) return false;
@@ -277,8 +277,9 @@ __global__ void __launch_bounds__(256) k_merge_count_hash(int32_t c, LayerSet la
 // flat order (equal columns in ascending layer order), sorted and folded by
 // rowsort.hpp, its columns and values four steps in flight.  Bound by latency
 // at 5 waves per SIMD: the register limit of launch bounds (96 instead of 108,
-// no spill) took the 16-layer merge from 1.17 to 1.06 ms; 80 registers spill
-// and take 1.12.
+// no spill) took the 16-layer merge from 1.17 to 1.06 ms, where 80 registers
+// spilled and took 1.12; now 0.95 (16 layers of 262,144 rows: this kernel 519 us,
+// 550 VALU instructions a row).
 template <int SR>
 __global__ void __launch_bounds__(256, 5) k_merge_sort(int32_t c, LayerSet layers, BinRef ref, const int64_t* out_rp,
                                                     int32_t* out_col, void* out_val) {

@@ -279,12 +279,11 @@ __global__ void __launch_bounds__(NT) k_num_hash(Csr A, Csr B, const int32_t* ro
     __shared__ __align__(4) uint8_t s_mark[SORT ? (T > 4 * SPG_WAVE ? T : 4 * SPG_WAVE) : 4];
     const int64_t i = rows[blockIdx.x];
     if constexpr (SORT) {
-        // Sorting costs by the product, the table by the slot and the output,
-        // and columns that repeat tend to lie in clusters, whose buckets
-        // overflow the networks.  So rows of up to 64 NU products and three per
-        // two outputs are sorted.  Four per output: R^T A of MIS-2 aggregates (two
-        // products per output) 76 against 62 us hashed, 64 grids batched 1.15
-        // against 0.93 ms; nine per eight: 0.94, uniform matrices the same.
+        // Sorting costs by the product, the table by the slot and the output, so
+        // rows of up to 64 NU products and three per two outputs are sorted.  64
+        // grids restricted by MIS-2 aggregates (R^T A has two products per output),
+        // batched: 0.94 ms; with four per output sorted 0.99, with nine per eight
+        // 0.94; uniform matrices the same.
         const int64_t f = flops[i], n = c_rp.count(i);
         if (!cnt_out && f <= NU * SPG_WAVE && f <= n + n / 2 && B.ncols <= RS_SPAN_MAX) {
             num_sort_row<SR, NU>(A, B, a_beg[i], a_end[i], (int32_t)f, lds.sort, s_mark, c_col, c_val, c_rp.off(i),

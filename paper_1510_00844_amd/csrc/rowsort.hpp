@@ -11,20 +11,19 @@
 // clusters overflow the networks; product rows of a span that a bitmap in the
 // keys' place can hold then take buckets of equal numbers of columns, the others
 // a bitonic sort of the whole row.  12 runs of 32 neighbouring columns a row, in
-// a window of 12,000 (262,144 rows): numeric 1865 us by the whole-row sort, 1045
-// by the ranks, 930 hashed, where the hash table orders its outputs by such a
-// bitmap too; in 190,000 (131,072 rows): 935 by the whole-row sort, 3150 hashed.
-// Equal
-// columns are then neighbours in ascending x, so the fold adds them in that
-// order, and the output positions are counted by ballots: consecutive lanes
-// write consecutive outputs.
+// a window of 12,000 (262,144 rows): numeric kernel 1867 us by the whole-row
+// sort, 961 by the ranks, 896 hashed, where the hash table orders its outputs by
+// such a bitmap too; in 190,000 (131,072 rows): 907 by the whole-row sort, 3117
+// hashed.  Equal columns are then neighbours in ascending x, so the fold adds them
+// in that order, and the output positions are counted by ballots: consecutive
+// lanes write consecutive outputs.
 //
 // Bound by instruction issue (a few hundred VALU instructions a row), so
 // everything is done per entry of the row, not per slot of a table: a row of
 // 256 entries is four steps, where the 512-slot table it took before cost eight
 // to clear, eight to compact and a probe loop per product (ER scale 18, 210K
-// rows of 270 products: 1248 -> 659 VALU instructions a row, 598 -> 491 us, now
-// at 5.5 TB/s past L2: the lines of the short B rows are used in part).
+// rows of 270 products: 1248 -> 609 VALU instructions a row, 598 -> 427 us, now
+// at 6.3 TB/s past L2: the lines of the short B rows are used in part).
 #pragma once
 #include "common.hpp"
 

@@ -622,8 +622,8 @@ static spg_status check_csr(const spg_csr* M, const char* name, spg_semiring sr,
 // grid to 2^32 threads in x, so one call takes at most 2^22 rows.
 static const int64_t MAX_ROWS_PER_CALL = 1ll << 22;
 
-// The product kernels add the lengths of up to 1024 B rows of one A row in
-// int32.  Those rows are distinct, so the sum is at most nnz(B), and each
+// The product kernels add the lengths of up to 960 B rows of one A row (1024 are
+// reckoned with) in int32.  Those rows are distinct, so the sum is at most nnz(B), and each
 // is at most ncols(B) long: it fits when either bound is below 2^31.
 static spg_status check_batch_sums(const spg_csr* B) {
     if (B->nnz >= (1ll << 31) - 1 && B->ncols * 1024 >= (1ll << 31) - 1)
@@ -744,7 +744,10 @@ static BinParams bin_params(spg_plan P, int64_t n) {
     // the bitmap pass records per-chunk counts of the numeric column chunks
     const int64_t W = P->opts.dense_chunk_cols;
     bp.chunk_counts = bp.dense_ok && ((n + W - 1) / W) <= MAX_CHUNKS;
-    // rank-space accumulator: (bits, prefix) words + capacity values must fit
+    // rank-space accumulator: the bitmap, its prefixes and the values must fit.
+    // 8 bytes are reckoned with for 32 columns, where the kernel takes 6: the line
+    // stands where the rank kernel was measured against the chunks, and wider B (from
+    // 353,000 columns on for 8192 outputs, 484,000 for 4096) is left to the chunks
     bp.rank_max_log2 = 0;
     if (bp.dense_ok) {
         const int64_t words = 2 * bitmap_bytes;
@@ -758,7 +761,7 @@ static BinParams bin_params(spg_plan P, int64_t n) {
 }
 
 // The product enumerators count a batch's products (the B-row lengths of up
-// to 1024 A entries) in int32, and step through them up to 1024 past the
+// to 960 A entries) in int32, and step through them up to 1024 past the
 // current one.  With n <= 2^19 (one LDS bitmap per row) a B row holds at
 // most 2^19 entries and a batch stays below 2^29; with wider B the rows that
 // enumerate whole B rows (hash bins) are bounded by their own products, so a

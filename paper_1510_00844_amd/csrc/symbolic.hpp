@@ -245,9 +245,9 @@ __global__ void __launch_bounds__(NT) k_sym_hash(Csr A, Csr B, BinRef ref, const
 // wave per row, four rows per workgroup, each wave with its own set of
 // SW_SLOTS int32 keys (at most 3/8 full).  The row's A entries are taken 64
 // at a time (wave_products): each lane holds one entry's B segment, a wave
-// scan gives the segment offsets, and each product is placed by a binary
-// search of the offsets across the lanes, its column inserted into the set.
-// New columns are counted.  No block-wide product enumeration and no
+// scan gives the segment offsets, each product finds its segment by the mark at
+// the segment's start and a running maximum, and its column is inserted into the
+// set.  New columns are counted.  No block-wide product enumeration and no
 // barriers: the rows of these bins are short.
 constexpr int SW_LOG2 = 10;
 constexpr int SW_SLOTS = 1 << SW_LOG2;
