@@ -84,16 +84,19 @@ __device__ inline int num_bin(int64_t flops, int64_t annz, int64_t cnt, bool sym
     return chunks_ok ? BIN_DENSE_PAR : BIN_DENSE;
 }
 
-// Whether a product's kernels are spread over the helper streams at all, from
-// the counts of a classification ([0, NBINS) rows, [NBINS, 2 NBINS) products) that
-// launches a kernel for every bin with rows from first_bin on.  A fork and a join
-// cost ten calls on the host and waits between the GPU's queues, 20 to 50 us a
-// phase; what they save is the latency of each further kernel, which is that of a
-// few rows however many it has: a bin's share of the work says little.  So: from six
-// kernels on (power-law matrices; uniform ones and stencils have fewer), and not
-// for few products.  One decision for both passes, from the symbolic bins: with
-// one pass spread and the other not, each was slower than alone (ER 21,083 x 55,716
-// x 32,369: 230 us both spread, 243 neither, 272 the symbolic pass only).
+// Work of a bin's kernel, from the counts of a classification ([0, NBINS) rows,
+// [NBINS, 2 NBINS) products).
+inline double bin_work(const int64_t* counts, int bin) {
+    return (double)counts[NBINS + bin] + 32.0 * (double)counts[bin];
+}
+
+// Whether a pass is spread over the helper streams at all, from the counts of a
+// classification that launches a kernel for every bin with rows from first_bin on.
+// A fork and a join cost ten calls on the host and waits between the GPU's queues,
+// 20 to 50 us a pass; what they save is the latency of each further kernel, which is
+// that of a few rows however many it has: a bin's share of the work says little.
+// So: from six kernels on (power-law matrices; uniform ones and stencils have
+// fewer), and not for few products.
 // Gain of four streams over one, whole products of random graphs of 1M to 400M
 // products, us by symbolic kernels: two to four -69 to -42, five -50 to -21, six -96
 // to 57, seven and more -26 to 193 (R-MAT scale 16, eight: 1948 -> 1924; the
@@ -108,6 +111,24 @@ inline bool worth_forking(const int64_t* counts, int first_bin) {
         kernels += b >= first_bin && counts[b] > 0;
     }
     return products >= FORK_MIN_PRODUCTS && kernels >= FORK_MIN_KERNELS;
+}
+// The numeric pass: spread where the symbolic pass was (one serial pass after one
+// that was spread was slower than either alone: ER 21,083 x 55,716 x 32,369 230 us
+// both spread, 243 neither, 272 the symbolic pass only), and also where its own
+// kernels, besides the copies of rows of one A entry, are as many and three of them
+// heavy: rank and rank-chunk kernels, whose workgroups the LDS limits, overlap well.
+// (The heavy rows of a product with predicted sizes, R-MAT of 58,877 rows, all of
+// them symbolic bitmap rows: 1648 us so, 1731 with the numeric pass on one stream.
+// With one or two heavy kernels the fork loses: R-MAT scale 13 148 / 154 us.)
+constexpr double HEAVY_SHARE = 0.1;
+inline bool worth_forking_numeric(const int64_t* counts, bool symbolic_spread) {
+    if (symbolic_spread) return true;
+    if (!worth_forking(counts, BIN_SMALL)) return false;
+    double total = 0;
+    for (int b = BIN_TINY; b < NBINS; ++b) total += bin_work(counts, b);
+    int heavy = 0;
+    for (int b = BIN_SMALL; b < NBINS; ++b) heavy += bin_work(counts, b) >= HEAVY_SHARE * total;
+    return heavy >= 3;
 }
 
 // The rows of one bin, located on the device: the per-bin row counts (the

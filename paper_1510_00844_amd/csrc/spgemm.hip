@@ -139,7 +139,7 @@ struct spg_plan_s {
     // calls can be captured into a HIP graph)
     bool frozen = false;
     bool have_symbolic = false;
-    bool spread = false;        // the product's kernels run on the helper streams too (decided by the symbolic pass)
+    bool spread = false;        // the symbolic pass ran on the helper streams too
     bool num_counts_valid = false;
     int64_t sym_counts[3 * NBINS];
     int64_t num_counts[4 * NBINS];
@@ -241,9 +241,6 @@ static spg_status join_streams(spg_plan P, int naux) {
 // the GPU between heavy kernels and small ones without shortening them), but
 // two whenever two bins have rows: the light bins then run beside the
 // heaviest one instead of after it.
-static double bin_work(const int64_t* counts, int bin) {
-    return (double)counts[NBINS + bin] + 32.0 * (double)counts[bin];
-}
 struct StreamLoad {
     double load[NAUX + 1] = {};
     int nstreams = 1;
@@ -1204,7 +1201,7 @@ static spg_status numeric_sr(spg_plan P, Csr a, Csr b, const int64_t* c_row_ptr,
         P->split_ready = true;
     }
     const std::vector<int> num_order = bins_by_work(P->num_counts, P->num_counts + NBINS);
-    StreamLoad nload(P, P->num_counts, P->spread);
+    StreamLoad nload(P, P->num_counts, worth_forking_numeric(P->num_counts, P->spread));
     SPG_TRY(fork_streams(P, nload.nstreams - 1));
     for (size_t oi = 0; oi < num_order.size(); ++oi) {
         const int bb = num_order[oi];

@@ -1,4 +1,4 @@
-"""The rule that spreads a product's kernels over the helper streams, on its lines."""
+"""The rules that spread a pass's kernels over the helper streams, on their lines."""
 
 import os
 import subprocess
@@ -24,6 +24,20 @@ static void expect(const char* what, std::initializer_list<int> bins, int64_t pr
         ++failed;
     }
 }
+// numeric bins with the given shares of 2^22 products
+static void numeric(const char* what, std::initializer_list<int> bins, std::initializer_list<double> shares, bool sym,
+                    bool want) {
+    int64_t c[2 * NBINS] = {};
+    auto s = shares.begin();
+    for (int b : bins) {
+        c[b] = 1;
+        c[NBINS + b] = (int64_t)(*s++ * (1 << 22));
+    }
+    if (worth_forking_numeric(c, sym) != want) {
+        std::printf("numeric, %s: not %d\n", what, (int)want);
+        ++failed;
+    }
+}
 int main() {
     const int64_t many = 1 << 20, few = many - 100;
     expect("five kernels", {2, 3, 4, 5, 12}, many, BIN_SMALL, false);
@@ -33,6 +47,11 @@ int main() {
     expect("six", {2, 3, 4, 5, 6, 12}, many, BIN_SMALL, true);
     expect("six, few products", {2, 3, 4, 5, 6, 12}, few, BIN_SMALL, false);
     expect("one", {5}, many, BIN_SMALL, false);
+    numeric("after a spread pass", {5}, {1.0}, true, true);
+    numeric("three heavy of six", {5, 6, 7, 11, 13, 14}, {.01, .01, .01, .6, .15, .22}, false, true);
+    numeric("two heavy of six", {5, 6, 7, 11, 13, 14}, {.01, .01, .01, .02, .75, .2}, false, false);
+    numeric("three heavy of five", {6, 7, 11, 13, 14}, {.02, .02, .6, .15, .21}, false, false);
+    numeric("three heavy of five, and rows of one A entry", {1, 6, 7, 11, 13, 14}, {.02, .01, .01, .6, .15, .21}, false, false);
     return failed;
 }
 """
