@@ -89,7 +89,7 @@ typedef struct {
     int32_t dense_chunk_cols;  /* numeric dense rows: columns per LDS chunk (2048, 4096, 8192 or 16384) */
     int32_t profile;           /* 1: time every kernel launch with HIP events */
     int32_t streams;           /* streams independent bins are spread over (1..4), at most: products of
-                                  fewer than 2^20 scalar products or fewer than six symbolic kernels
+                                  fewer than 2^20 scalar products or fewer than six kernels a pass
                                   run on the plan's stream alone */
     int32_t gather_map;        /* numeric heavy rows, products per lane: 1 = neighbouring lanes take
                                   neighbouring products (coalesced), 2 = each lane a contiguous range */

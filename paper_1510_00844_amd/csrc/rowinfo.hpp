@@ -115,19 +115,23 @@ inline bool worth_forking(const int64_t* counts, int first_bin) {
 // The numeric pass: spread where the symbolic pass was (one serial pass after one
 // that was spread was slower than either alone: ER 21,083 x 55,716 x 32,369 230 us
 // both spread, 243 neither, 272 the symbolic pass only), and also where its own
-// kernels, besides the copies of rows of one A entry, are as many and three of them
-// heavy: rank and rank-chunk kernels, whose workgroups the LDS limits, overlap well.
-// (The heavy rows of a product with predicted sizes, R-MAT of 58,877 rows, all of
-// them symbolic bitmap rows: 1648 us so, 1731 with the numeric pass on one stream.
-// With one or two heavy kernels the fork loses: R-MAT scale 13 148 / 154 us.)
-constexpr double HEAVY_SHARE = 0.1;
+// kernels, besides the copies of rows of one A entry, are as many and the three kinds
+// with a bitmap's ranks (rank chunks, two capacities of whole rows) share its work:
+// their workgroups, which the LDS limits, overlap well.  The heavy rows of a product
+// with predicted sizes, all of them symbolic bitmap rows, whole call on one stream and
+// on several: R-MAT scale 16, 16 entries a row (78, 15 and 7% of the work) 2331 / 2158
+// us, 8 a row (51, 29, 17%) 1431 / 1337, scale 15 (57, 28, 14%) 986 / 940.  Hash and
+// rank kernels of few rows lose: R-MAT 13,550 x 20,699 x 9387 225 / 275 us, two rank
+// kernels SSCA 12,249 243 / 293.
+constexpr double HEAVY_SHARE = 0.05;
 inline bool worth_forking_numeric(const int64_t* counts, bool symbolic_spread) {
     if (symbolic_spread) return true;
     if (!worth_forking(counts, BIN_SMALL)) return false;
     double total = 0;
     for (int b = BIN_TINY; b < NBINS; ++b) total += bin_work(counts, b);
     int heavy = 0;
-    for (int b = BIN_SMALL; b < NBINS; ++b) heavy += bin_work(counts, b) >= HEAVY_SHARE * total;
+    for (int b : {BIN_DENSE_PAR, BIN_RANK0, BIN_RANK0 + 1, BIN_RANK0 + 2})
+        heavy += bin_work(counts, b) >= HEAVY_SHARE * total;
     return heavy >= 3;
 }
 

@@ -49,6 +49,9 @@ int main() {
     expect("one", {5}, many, BIN_SMALL, false);
     numeric("after a spread pass", {5}, {1.0}, true, true);
     numeric("three heavy of six", {5, 6, 7, 11, 13, 14}, {.01, .01, .01, .6, .15, .22}, false, true);
+    numeric("three rank kernels of seven, one with a fifteenth", {5, 6, 7, 8, 11, 13, 14},
+            {.001, .001, .002, .002, .78, .068, .146}, false, true);
+    numeric("three heavy hash kernels of six", {2, 3, 4, 5, 6, 13}, {.02, .02, .1, .1, .1, .66}, false, false);
     numeric("two heavy of six", {5, 6, 7, 11, 13, 14}, {.01, .01, .01, .02, .75, .2}, false, false);
     numeric("three heavy of five", {6, 7, 11, 13, 14}, {.02, .02, .6, .15, .21}, false, false);
     numeric("three heavy of five, and rows of one A entry", {1, 6, 7, 11, 13, 14}, {.02, .01, .01, .6, .15, .21}, false, false);
